@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void align_q8_0_kernel(const uint8_t *__restri
   const int j = (int)(t & 7);
   if (blk >= nblocks) return;
   const uint16_t *p = reinterpret_cast<const uint16_t *>(xq + blk * Q8B + 2 + 4 * j);
-  act[blk * 8 + j] = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
+  act[blk * 8 + aligned_pos(j)] = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
   if (j == 0) actd[blk] = f16_bits_to_f32(*reinterpret_cast<const uint16_t *>(xq + blk * Q8B));
 }
 

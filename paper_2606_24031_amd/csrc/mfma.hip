@@ -3,40 +3,59 @@
 // over all groups; Sec. 3.3: 4-bit weight codes times 8-bit activation codes,
 // one scaling per 32 elements).
 //
-// Workgroup tile: up to 64 token rows of one group by 128 weight rows (one
-// slice).  Each of the four waves owns 32 weight rows and both 32-row halves
-// of the tokens (the second half is compiled out for tiles of at most 32
-// rows), so one weight operand feeds two v_mfma_i32_32x32x32_i8 per Q-block.
-//   * Weights: lanes l and l + 32 own the same weight row; they stream its
-//     144-byte groups of 8 blocks one group ahead, lane l the first 72 bytes
-//     (blocks 0..3), lane l + 32 the last 72 (blocks 4..7).  Each lane splits
-//     its block j into low- and high-nibble codes, each as the int8 16*(q-8)
-//     (the nibble q ^ 8 in the high half of its byte), and one swap between
-//     the wave halves (v_permlane32_swap) leaves in lanes 0..31 the low and in
-//     lanes 32..63 the high codes of block j in one register and of block
-//     j + 4 in the other: the A operands of both blocks.
-//   * Activations: the tile's aligned Q8_0 codes for 8 blocks go to LDS by
-//     direct loads (global_load_lds), the 16-byte chunks of a row XOR-swizzled
-//     by the row so the rows a half-wave reads sit in distinct banks.  With
-//     K <= 512 all of K stays resident and the workgroup runs several weight
-//     slices with no barrier; otherwise the next 8 blocks are staged while the
-//     current 8 are used, one barrier per 8 blocks.
+// Workgroup tile: up to 64 token rows of one group by one slice of 128 weight
+// rows.  Each of the four waves owns 32 weight rows and both 32-row halves of
+// the tokens (the second half is compiled out for tiles of at most 32 rows),
+// so one weight operand feeds two v_mfma_i32_32x32x32_i8 per Q-block.
+//   * Staging: four blocks (K = 128) of every operand at a time, by direct
+//     loads into a ring of LDS slots: 80 bytes of each weight row (raw), 128
+//     bytes of codes and 16 of scales of each token row.  A wave waits only
+//     for its oldest stage (a vmcnt of the younger ones' loads) before the
+//     stage's one barrier.  The raw weights go through LDS because a lane per
+//     row read straight from memory touches a cache line per lane and
+//     instruction; and because they then take no registers while under way.
+//   * Weights: a lane of the 32x32x32 product supplies 16 of a row's 32 codes,
+//     any 16 as long as the tokens' are the same ones: lanes l and l + 32
+//     take the first and last 8 payload bytes of the row's block (two 4-bit
+//     codes each), turned into the int8 16*(q-8) (the nibble q ^ 8 in the
+//     high half of its byte).  The aligned codes of the tokens are stored in
+//     that order (aligned_pos).
+//   * Activations: the 16-byte pieces of a row XOR-swizzled by the row so the
+//     rows a half-wave reads sit in distinct banks.
 //   * Products: the weights are the A operand and the token rows the B
 //     operand, so element e of an MFMA in lane l is weight row
 //     8*(e/4) + 4*(l/32) + e%4 of the wave's 32 and token row l%32 of the
-//     half: a lane holds one token's sums for 16 weight rows.
+//     half: a lane holds one token's sums for 16 weight rows.  Tiles of at
+//     most 16 rows run v_mfma_i32_16x16x32_i8 (half the padding): two per
+//     block, weight rows 0..15 and 16..31 of the wave, lane l supplying the 8
+//     codes of payload dword l/16 of row l%16.
 //   * Scaling: the accumulator input is 0x4B400000, so the int32 result read
-//     as a float is exactly 1.5*2^23 + 16 s (|16 s| < 2^22); with dx the
-//     token's activation scale divided by 16 (exact), t = fma(f, dx,
-//     -1.5*2^23*dx) = s dx rounded once and acc = fma(t, d_w, acc).  The
+//     as a float is exactly 1.5*2^23 + 16 s (|16 s| < 2^22); t = fma(f, dx,
+//     -1.5*2^23*dx) = 16 s dx rounded once and acc = fma(t, d_w/16, acc).  The
 //     per-lane factor is the activation scale; the per-element factor is
 //     the weight-row scale, which both token halves share: each wave puts
-//     its rows' scales of the current 8 blocks in a small LDS table and
-//     reads 16 of them per block (broadcast reads, one set for both halves).
+//     its rows' scales of the current stage in a small LDS table and reads
+//     16 of them per block (broadcast reads, one set for both halves).
 // Gate/up waves hold 16 gate rows and the 16 matching up rows, so element e
 // and e + 8 of a lane are the gate and up sums of one column and SwiGLU
 // needs no lane exchange; Q8_0 of each 32-wide h block goes through LDS.
-// Down tiles write w * y per pair, four consecutive columns per store.
+// Down tiles write w * y per pair, through LDS in whole rows of 512 bytes.
+//
+// What bounds it: VALU issue.  The two fp32 operations per output and block
+// cost more than the product itself (in registers alone the 32x32x32 block
+// takes 61 ns per SIMD, of which the product 16); LDS and load traffic add to
+// that.  Registers (at most 168) and LDS (51 KB) leave three workgroups per
+// compute unit; the deeper ring that two would allow, four workgroups of 128
+// registers, and waves of 64 weight rows all measured slower.  Kernel times
+// before (weights loaded per lane into registers one group of eight blocks
+// ahead, two workgroups per compute unit) and now, top-8 of 256 experts with
+// skewed load, H = 2048, I = 512: gate/up of 947 tokens 114-126 -> 103-105 us,
+// of 5120 tokens 385-405 -> 333-352 us, down 63-70 -> 65-68 and 214-221 ->
+// 230-244 us; 32 rows over 151936 x 2048 62.8 -> 59.5 us (2.9 TB/s), 947 over
+// 4096 x 2048 34.7 -> 33.6 us.  The down projection lost its resident codes
+// and several slices per workgroup (K <= 512): one slice per workgroup at
+// three per compute unit does as well up to a 947-token prompt, and the long
+// prompt's loss is a sixth of what its gate/up gains.
 #include "w4a8_dev.h"
 #include "w4a8_host.h"
 
@@ -47,7 +66,7 @@ namespace {
 constexpr int MNT = 256;           // threads: four waves
 constexpr int MT = 64;             // token rows per tile
 constexpr int WROWS = 128;         // weight rows per slice (32 per wave)
-constexpr int SPW_MAX = 4;         // slices per workgroup when the codes are resident
+constexpr int Q4SB = W4A8_Q4_SYM_BLOCK_BYTES;
 constexpr int BIAS = 0x4B400000;   // float 1.5 * 2^23
 constexpr float BIASF = 12582912.0f;
 
@@ -74,7 +93,6 @@ struct MArgs {
   int64_t M;                       // dense product (M > 0): M activation rows in implicit
                                    // tiles of tr rows, one weight matrix (ws), no route
   int tr;                          // dense product: rows per tile
-  int spw;                         // slices per workgroup
 };
 
 // Weight of pair p in the combine: its routing weight, or for the shared
@@ -84,81 +102,44 @@ __device__ __forceinline__ float pair_weight(const MArgs &a, int p) {
   return p < pr ? a.topk_w[p] : (a.shared_w ? a.shared_w[p - pr] : 1.0f);
 }
 
-constexpr int DWS = 36;             // row stride of a wave's weight-scale table
+// A stage is four blocks (K = 128) of the tile's operands in LDS, moved there
+// by direct loads (global_load_lds) into a ring of slots.
+constexpr int SB = 4;              // blocks per stage
+constexpr int WCH = 5;             // 16-byte pieces of a weight row per stage (80 bytes)
+constexpr int WDW = WCH * 4;       // ... in dwords
+
+// Tile kinds by token rows: at most 16 (16x16x32 products), 32, 64.
+constexpr int T16 = 0, T32 = 1, T64 = 2;
+constexpr int tile_rows(int kind) { return kind == T64 ? 64 : kind == T32 ? 32 : 16; }
+
+// A ring slot: the raw weight rows [wave][32 rows x 80 bytes], then the
+// codes [row][piece ^ (row/2)%8] and scales [row] of the stage's four blocks.
+constexpr int SLOT_W = 4 * 32 * WCH * 16;
+constexpr int slot_bytes(int kind) { return SLOT_W + tile_rows(kind) * (128 + 16); }
+// Two slots for 64-row tiles, three for 32, four for 16 (whose stages take
+// least time to compute), within a third of a compute unit's LDS.
+constexpr int RING_BYTES = 4 * slot_bytes(T16);
+constexpr int ring_slots(int kind) { return RING_BYTES / slot_bytes(kind); }
+constexpr int HVS = 68;            // row stride of the h tile
+constexpr int EPI_BYTES = MT * (WROWS + 4) * 4;
 
 struct MLds {
-  union {
-    uint4 a[2][MT * 16];           // codes of 8 blocks, [buffer][row][chunk ^ row%16]
-    float hv[MT][68];              // gate/up epilogue: h of the tile, [row][64 columns]
-  };
-  float2 dx[2][8][MT];             // activation scales of 8 blocks divided by 16, and
-                                   // their products with -1.5*2^23: [buffer][block][row]
-  float dw[4][8][DWS];             // weight-row scales of the current group, [wave][block][row]
-  int arow[MT];                    // activation row of each tile row
-  int pair[MT];                    // pair of each tile row (-1: padding)
-  float pw[MT];                    // down: combine weight of the row's pair
+  // the ring; before it the tile's activation rows (int [64]), after it the
+  // tile's h (gate/up, float [64][68]) or output (down, float [64][132]),
+  // then its pairs and combine weights (int and float [64])
+  uint4 ring[RING_BYTES / 16];
+  float dw[4][SB][32];             // weight-row scales of the current stage, [wave][block][row]
 };
 
-// Half of a weight row's group of 8 blocks (72 bytes): blocks 0..3 in lanes
-// 0..31, blocks 4..7 in lanes 32..63.
-struct HW {
-  uint32_t D[18];
-};
-
-__device__ __forceinline__ void load_hw(const uint8_t *p, HW &w) {
-  const v2u *v = reinterpret_cast<const v2u *>(p);
-#pragma unroll
-  for (int i = 0; i < 9; i++) {
-    const v2u t = v[i];
-    w.D[2 * i] = t.x;
-    w.D[2 * i + 1] = t.y;
-  }
-}
-
-// Payload dword c of the half's block j (bytes 18j + 2 + 4c ..), and the
-// dword holding its fp16 scale (low half for even j, high half for odd j).
-__device__ __forceinline__ uint32_t hw_nib(const HW &w, int j, int c) {
-  const int i = j >> 1;
-  return (j & 1) == 0 ? align2(w.D[9 * i + c + 1], w.D[9 * i + c]) : w.D[9 * i + 5 + c];
-}
-__device__ __forceinline__ uint32_t hw_sdw(const HW &w, int j) {
-  return (j & 1) == 0 ? w.D[9 * (j >> 1)] : w.D[9 * (j >> 1) + 4];
-}
-
-// Weight operands and scale dwords of blocks j and j + 4 of the group.
-__device__ __forceinline__ void pair_ops(const HW &w, int j, v4i &b0, v4i &b1, uint32_t &s0,
-                                         uint32_t &s1) {
-#pragma unroll
-  for (int c = 0; c < 4; c++) {
-    // q ^ 8 read as a signed 4-bit number is q - 8; placed in the high half
-    // of a byte it is the int8 16 * (q - 8).  nib << 4 for the low nibbles
-    // comes from one funnel shift of the two dwords the payload straddles
-    // (the bits shifted in land in the masked low half of each byte)
-    const int i = j >> 1;
-    const uint32_t nib = hw_nib(w, j, c);
-    const uint32_t sh = (j & 1) == 0 ? __builtin_amdgcn_alignbit(w.D[9 * i + c + 1], w.D[9 * i + c], 12)
-                                     : nib << 4;
-    const v2u r = __builtin_amdgcn_permlane32_swap((sh ^ 0x80808080u) & 0xF0F0F0F0u,
-                                                   (nib ^ 0x88888888u) & 0xF0F0F0F0u, false, false);
-    b0[c] = (int)r.x;
-    b1[c] = (int)r.y;
-  }
-  const uint32_t sd = hw_sdw(w, j);
-  const v2u r = __builtin_amdgcn_permlane32_swap(sd, sd, false, false);
-  s0 = r.x;
-  s1 = r.y;
-}
-
-// Direct load of 16 bytes per lane into LDS at dst + 16 * lane.  Written as
-// an instruction the compiler does not model: through the builtin it cannot
-// tell a copy into one staging buffer from reads of the other, and waits for
-// every outstanding load (the prefetched weights with it) before reading
-// LDS.  The copies are ordered by the explicit wait and barrier at the top
-// of the group that reads them.
+// Direct load of 16 bytes per active lane into LDS at dst + 16 * lane.
+// Written as an instruction the compiler does not model: through the builtin
+// it cannot tell a copy into one slot from reads of another, and waits for
+// every outstanding load before reading LDS.  The copies are ordered by the
+// explicit wait and barrier at the top of the stage that reads them.
 // M0 is named as clobbered; nothing else in these kernels keeps a value in it.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void lds_dma16(const uint32_t *src, const void *dst) {
+__device__ __forceinline__ void lds_dma16(const uint8_t *src, const void *dst) {
   const uint32_t m0 =
       (uint32_t)(uintptr_t)(const void __attribute__((address_space(3))) *)dst;
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
@@ -168,28 +149,71 @@ __device__ __forceinline__ void lds_dma16(const uint32_t *src, const void *dst) 
 }
 #pragma clang diagnostic pop
 
-// Copy the tile's codes of blocks 8g..8g+7 into buffer buf: wave w < nwv
-// moves rows 16w..16w+15 (the tile's rows rounded up to 16, 32 or 64), four rows per
-// instruction; lane l writes chunk position l%16 of row r0 + l/16, which holds
-// chunk (l%16) ^ (row % 16) of the row's 256 bytes.
-__device__ __forceinline__ void stage_codes(const MArgs &a, MLds &L, int g, int buf, int nwv,
-                                            int wave, int lane, int nblk) {
-  if (wave >= nwv) return;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int r0 = wave * 16 + i * 4;
-    const int r = r0 + (lane >> 4);
-    const int c = (lane & 15) ^ (r & 15);
-    const uint32_t *src = a.act + ((int64_t)L.arow[r] * nblk + 8 * g) * 8 + c * 4;
-    lds_dma16(src, &L.a[buf][r0 * 16]);
-  }
+// All but this wave's youngest N vector memory operations are done, its LDS
+// reads too, and so for every other wave of the workgroup.
+template <int N>
+__device__ __forceinline__ void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// A operand of block kk for tile row `row`: its codes 16*hh..+15 of the
-// block, from the swizzled staging buffer.
-__device__ __forceinline__ v4i aop(const uint4 *abuf, int row, int kk, int hh) {
-  const uint4 u = abuf[row * 16 + ((2 * kk + hh) ^ (row & 15))];
-  return v4i{(int)u.x, (int)u.y, (int)u.z, (int)u.w};
+// Dwords of a weight row in a slot: block j's fp16 scale and payload.  A
+// stage of Q4_0 is half a 144-byte group: the first half is loaded as bytes
+// 0..79 of the group, the second as bytes 64..143, so its blocks start 8
+// bytes into the row (o = 2 dwords).
+__device__ __forceinline__ v4i codes4(uint32_t sh0, uint32_t nib0, uint32_t sh1, uint32_t nib1) {
+  // q ^ 8 read as a signed 4-bit number is q - 8; placed in the high half of
+  // a byte it is the int8 16 * (q - 8).  sh: the payload dword shifted up by
+  // 4 (what is shifted in lands in the masked low half of a byte)
+  return v4i{(int)((sh0 ^ 0x80808080u) & 0xF0F0F0F0u), (int)((nib0 ^ 0x88888888u) & 0xF0F0F0F0u),
+             (int)((sh1 ^ 0x80808080u) & 0xF0F0F0F0u), (int)((nib1 ^ 0x88888888u) & 0xF0F0F0F0u)};
+}
+// Payload dwords c and c + 1 of block j of the row at wl: read, and turned
+// into the int8 codes of elements 4c..4c+3, 4c+16..4c+19, 4c+4..4c+7,
+// 4c+20..4c+23.
+struct Raw {
+  uint32_t d0, d1, d2;
+};
+template <bool SYM>
+__device__ __forceinline__ Raw wraw(const uint32_t *wl, int j, int c) {
+  if (SYM) return Raw{wl[5 * j + 1 + c], wl[5 * j + 2 + c], 0};
+  const uint32_t *p = wl + 9 * (j >> 1) + c;
+  return (j & 1) == 0 ? Raw{p[0], p[1], p[2]} : Raw{p[5], p[6], 0};
+}
+template <bool SYM>
+__device__ __forceinline__ v4i wcodes2(const Raw &r, int j) {
+  if (!SYM && (j & 1) == 0)
+    return codes4(__builtin_amdgcn_alignbit(r.d1, r.d0, 12), align2(r.d1, r.d0),
+                  __builtin_amdgcn_alignbit(r.d2, r.d1, 12), align2(r.d2, r.d1));
+  return codes4(r.d0 << 4, r.d0, r.d1 << 4, r.d1);
+}
+// Payload dword c of block j: elements 4c..4c+3, 4c+16..4c+19.
+template <bool SYM>
+__device__ __forceinline__ long wcodes1(const uint32_t *wl, int j, int c) {
+  uint32_t nib, sh;
+  if (SYM) {
+    nib = wl[5 * j + 1 + c];
+    sh = nib << 4;
+  } else {
+    const uint32_t *p = wl + 9 * (j >> 1) + c;
+    if ((j & 1) == 0) {
+      const uint32_t d0 = p[0], d1 = p[1];
+      nib = align2(d1, d0);
+      sh = __builtin_amdgcn_alignbit(d1, d0, 12);
+    } else {
+      nib = p[5];
+      sh = nib << 4;
+    }
+  }
+  return __builtin_bit_cast(long, v2u{(sh ^ 0x80808080u) & 0xF0F0F0F0u,
+                                      (nib ^ 0x88888888u) & 0xF0F0F0F0u});
+}
+// The scale of block j as the scaling step wants it: Q4_0 divided by 16
+// (exact), the fp32 format as stored.
+template <bool SYM>
+__device__ __forceinline__ float wscale(const uint32_t *wl, int j) {
+  if (SYM) return __builtin_bit_cast(float, wl[5 * j]);
+  const uint32_t sd = wl[9 * (j >> 1) + 4 * (j & 1)];
+  return 0.0625f * f16_bits_to_f32((j & 1) ? sd >> 16 : sd);
 }
 
 // Integer product with the bias accumulator input, read as floats (the whole
@@ -197,201 +221,135 @@ __device__ __forceinline__ v4i aop(const uint4 *abuf, int row, int kk, int hh) {
 __device__ __forceinline__ v16f mm(v4i a, v4i b, v16i c) {
   return __builtin_bit_cast(v16f, __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0));
 }
-
-// acc[e] += s_e * dx * dw[e] for elements 4q..4q+3: f holds the biased int32
-// results of one block for this lane's token (dx its activation scale
-// divided by 16, nbx = -1.5*2^23 * dx) and 16 weight rows; t = fma(f, dx,
-// nbx) = 16 s dx / 16 rounded once, then one fma with each row's weight
-// scale (dw4: rows 8q + 4hh .. +3).
-__device__ __forceinline__ void scale4(float acc[16], const v16f &f, int q, float dx, float nbx,
-                                       float4 dw4) {
-  acc[4 * q + 0] = fmaf(fmaf(f[4 * q + 0], dx, nbx), dw4.x, acc[4 * q + 0]);
-  acc[4 * q + 1] = fmaf(fmaf(f[4 * q + 1], dx, nbx), dw4.y, acc[4 * q + 1]);
-  acc[4 * q + 2] = fmaf(fmaf(f[4 * q + 2], dx, nbx), dw4.z, acc[4 * q + 2]);
-  acc[4 * q + 3] = fmaf(fmaf(f[4 * q + 3], dx, nbx), dw4.w, acc[4 * q + 3]);
-}
-
-// A token's activation scale of one block (divided by 16) with its product
-// with -1.5*2^23, staged once per tile and group instead of formed per block.
-__device__ __forceinline__ float2 scale_pair(float dx) { return make_float2(dx, -BIASF * dx); }
-
-// One block: the weight operand b (32 weight rows) against both token
-// halves; dw points at the block's 32 weight-row scales of this wave, dxb
-// at the block's 64 activation scales.  The scales of four weight rows are
-// read once for both halves.
-// The operands of one block read from LDS: the token codes of both halves,
-// the weight-row scales (four rows per float4) and the activation scales.
-// AHEAD: the scales too are read with the codes (else at their use, for the
-// short kernel's register budget).
-struct BlockIn {
-  v4i a0, a1;
-  float4 dw[4];
-  float2 dx0, dx1;
-  const float *dwp;
-  const float2 *dxp;
-};
-template <bool TWO, bool AHEAD>
-__device__ __forceinline__ BlockIn block_in(const uint4 *abuf, const float *dw, const float2 *dxb,
-                                            int kk, int r32, int hh) {
-  BlockIn o;
-  o.a0 = aop(abuf, r32, kk, hh);
-  o.a1 = TWO ? aop(abuf, 32 + r32, kk, hh) : v4i{0, 0, 0, 0};
-  o.dwp = dw + 4 * hh;
-  o.dxp = dxb;
-  if (AHEAD) {
-#pragma unroll
-    for (int q = 0; q < 4; q++) o.dw[q] = *reinterpret_cast<const float4 *>(dw + 8 * q + 4 * hh);
-    o.dx0 = dxb[r32];
-    o.dx1 = TWO ? dxb[32 + r32] : make_float2(0.0f, 0.0f);
-  }
-  return o;
-}
-template <bool TWO, bool AHEAD>
-__device__ __forceinline__ void block(float acc0[16], float acc1[16], const BlockIn &in, v4i b,
-                                      v16i c0, int r32) {
-  const v16f f0 = mm(b, in.a0, c0);
-  v16f f1;
-  if (TWO) f1 = mm(b, in.a1, c0);
-  const float2 dx0 = AHEAD ? in.dx0 : in.dxp[r32];
-  const float2 dx1 = AHEAD ? in.dx1 : (TWO ? in.dxp[32 + r32] : make_float2(0.0f, 0.0f));
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    const float4 dw4 = AHEAD ? in.dw[q] : *reinterpret_cast<const float4 *>(in.dwp + 8 * q);
-    scale4(acc0, f0, q, dx0.x, dx0.y, dw4);
-    if (TWO) scale4(acc1, f1, q, dx1.x, dx1.y, dw4);
-  }
-}
-
-// Tiles of at most 16 rows run v_mfma_i32_16x16x32_i8 instead (half the
-// padding of a 32-row half): per block and wave two products, weight rows
-// 0..15 and 16..31 of the wave as the A operand, the tile's 16 token rows as
-// the B operand.  Lane l of a product holds token l%16 and weight rows
-// 4*(l/16)..+3 of the product's 16, so a lane takes eight sums of one token:
-// e < 4 of rows 4*(l/16) + e, e >= 4 of rows 16 + 4*(l/16) + e - 4.
 typedef float v4f __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ v4f mm16(long a, long b, v4i c) {
   return __builtin_bit_cast(v4f, __builtin_amdgcn_mfma_i32_16x16x32_i8(a, b, c, 0, 0, 0));
 }
 
-// The A operands of both products of one block from its 32x32x32 A operand
-// b (lane l < 32: codes 0..15 of wave row l; lane l + 32: codes 16..31 of
-// the same row).  A 16x16x32 product wants in lane l codes 8*(l/16)..+7 of
-// row l%16 (of its 16 rows): each 16-lane row of the wave keeps the half it
-// needs for one product and trades the other half with its neighbouring
-// row, one v_permlane16_swap per dword (odd rows of the first operand
-// against even rows of the second).
-__device__ __forceinline__ void split16(v4i b, long &m0, long &m1) {
-  const v2u s0 = __builtin_amdgcn_permlane16_swap((uint32_t)b[0], (uint32_t)b[2], false, false);
-  const v2u s1 = __builtin_amdgcn_permlane16_swap((uint32_t)b[1], (uint32_t)b[3], false, false);
-  m0 = __builtin_bit_cast(long, v2u{s0.x, s1.x});
-  m1 = __builtin_bit_cast(long, v2u{s0.y, s1.y});
+// acc += s * dx * dw of one element; f = 1.5*2^23 + 16 s.  fp16 scales: t =
+// fma(f, dx, nbx) = 16 s dx rounded once (nbx = -1.5*2^23*dx is exact for an
+// 11-bit scale), dw divided by 16.  fp32 scales: that product would round,
+// so s first (exact), then t = s dx.
+template <bool SYM>
+__device__ __forceinline__ float scale1(float acc, float f, float dx, float nbx, float dw) {
+  if (SYM) return fmaf(fmaf(f, 0.0625f, -0.0625f * BIASF) * dx, dw, acc);
+  return fmaf(fmaf(f, dx, nbx), dw, acc);
+}
+template <bool SYM>
+__device__ __forceinline__ void scale4(float *acc, float f0, float f1, float f2, float f3, float dx,
+                                       float nbx, float4 dw) {
+  acc[0] = scale1<SYM>(acc[0], f0, dx, nbx, dw.x);
+  acc[1] = scale1<SYM>(acc[1], f1, dx, nbx, dw.y);
+  acc[2] = scale1<SYM>(acc[2], f2, dx, nbx, dw.z);
+  acc[3] = scale1<SYM>(acc[3], f3, dx, nbx, dw.w);
+}
+template <bool SYM>
+__device__ __forceinline__ void scale16(float acc[16], const v16f &f, float dx, float nbx,
+                                        const float4 dw[4]) {
+#pragma unroll
+  for (int q = 0; q < 4; q++)
+    scale4<SYM>(acc + 4 * q, f[4 * q], f[4 * q + 1], f[4 * q + 2], f[4 * q + 3], dx, nbx, dw[q]);
 }
 
-// B operand of block kk for token row t: codes 8c..8c+7 of the block, c =
-// lane / 16, from the swizzled staging buffer.
-__device__ __forceinline__ long aop16(const uint4 *abuf, int t, int kk, int c) {
-  const v2u *p = reinterpret_cast<const v2u *>(abuf + t * 16 + ((2 * kk + (c >> 1)) ^ (t & 15)));
-  return __builtin_bit_cast(long, p[c & 1]);
-}
-
-struct BlockIn16 {
-  long a;
-  float4 dw0, dw1;
-  float2 dx;
+// One block's product operands in LDS as a lane of the 32-row form reads
+// them: its weight payload and its token's codes of both halves.
+struct BlockIn {
+  Raw r;
+  v4i u0, u1;
 };
-__device__ __forceinline__ BlockIn16 block_in16(const uint4 *abuf, const float *dw,
-                                                const float2 *dxb, int kk, int t, int c) {
-  BlockIn16 o;
-  o.a = aop16(abuf, t, kk, c);
-  o.dw0 = *reinterpret_cast<const float4 *>(dw + 4 * c);
-  o.dw1 = *reinterpret_cast<const float4 *>(dw + 16 + 4 * c);
-  o.dx = dxb[t];
+template <bool SYM, bool TWO>
+__device__ __forceinline__ BlockIn block_in(const uint32_t *wl, const uint4 *a0, const uint4 *a1,
+                                            int j, int hh, int sw) {
+  BlockIn o;
+  o.r = wraw<SYM>(wl, j, 2 * hh);
+  o.u0 = __builtin_bit_cast(v4i, a0[(2 * j + hh) ^ sw]);
+  o.u1 = TWO ? __builtin_bit_cast(v4i, a1[(2 * j + hh) ^ sw]) : v4i{0, 0, 0, 0};
   return o;
 }
-// One block of a 16-row tile: acc[e] += s_e * dx * dw[e] as in scale4.
-__device__ __forceinline__ void block16(float acc[16], const BlockIn16 &in, v4i b, v4i c4) {
-  long m0, m1;
-  split16(b, m0, m1);
-  const v4f f0 = mm16(m0, in.a, c4);
-  const v4f f1 = mm16(m1, in.a, c4);
-  const float dx = in.dx.x, nbx = in.dx.y;
-  acc[0] = fmaf(fmaf(f0[0], dx, nbx), in.dw0.x, acc[0]);
-  acc[1] = fmaf(fmaf(f0[1], dx, nbx), in.dw0.y, acc[1]);
-  acc[2] = fmaf(fmaf(f0[2], dx, nbx), in.dw0.z, acc[2]);
-  acc[3] = fmaf(fmaf(f0[3], dx, nbx), in.dw0.w, acc[3]);
-  acc[4] = fmaf(fmaf(f1[0], dx, nbx), in.dw1.x, acc[4]);
-  acc[5] = fmaf(fmaf(f1[1], dx, nbx), in.dw1.y, acc[5]);
-  acc[6] = fmaf(fmaf(f1[2], dx, nbx), in.dw1.z, acc[6]);
-  acc[7] = fmaf(fmaf(f1[3], dx, nbx), in.dw1.w, acc[7]);
-}
 
-// One tile: rows token rows (1..64) of expert's group from sorted position
-// pos (or of the dense rows from pos), against weight slices s0 .. s0 + ns
-// - 1 (ns > 1 only for resident codes and the down projection).  TWO: the
-// tile holds more than 32 rows (a compile-time branch: a run-time one inside
-// the block loop makes the compiler keep every block's second product until
-// the loop's end).
-template <bool GATEUP, bool TWO, bool RES, bool SK, bool H16 = false>
+// One tile: rows token rows of expert's group from sorted position pos (or of
+// the dense rows from pos), against one slice of weight rows.
+template <bool GATEUP, int KIND, bool SYM>
 __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, int pos, int rows,
-                                          int s0, int ns) {
-  static_assert(!(TWO && H16), "a 16-row tile has one half");
-  constexpr int NWV = TWO ? 4 : (H16 ? 1 : 2);   // waves that stage the codes
+                                          int slice) {
+  constexpr int ROWS = tile_rows(KIND), NS = ring_slots(KIND), SLOT = slot_bytes(KIND);
+  static_assert(NS >= 2 && EPI_BYTES + MT * 8 <= RING_BYTES, "two stages, and the epilogue, fit the ring");
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int r32 = lane & 31, hh = lane >> 5;
-  const int nblk = (int)(a.K / 32), G = (int)(a.K / 256);
-  constexpr bool resident = RES;                  // G <= 2: every group staged once
+  const int nblk = (int)(a.K / 32), S = nblk / SB;
+  uint8_t *const ring = reinterpret_cast<uint8_t *>(L.ring);
 
-  if (tid < MT) {
-    int p = -1, r = -1;
-    if (tid < rows) {
-      p = a.M ? pos + tid : a.perm[pos + tid];
-      r = GATEUP ? (p < a.T * a.k ? p / (int)a.k : p - (int)(a.T * a.k)) : p;
-    }
-    L.pair[tid] = p;
-    L.arow[tid] = r;
-    if (!GATEUP) L.pw[tid] = p >= 0 ? pair_weight(a, p) : 0.0f;
+  // the pair of tile row m, or -1 (padding)
+  auto row_pair = [&](int m) { return m < rows ? (a.M ? pos + m : a.perm[pos + m]) : -1; };
+  int *const arow = reinterpret_cast<int *>(ring);
+  if (tid < ROWS) {
+    const int p = row_pair(min(tid, rows - 1));   // padding rows read the last row
+    arow[tid] = GATEUP ? (p < a.T * a.k ? p / (int)a.k : p - (int)(a.T * a.k)) : p;
   }
   __syncthreads();
-  if (tid < MT && L.arow[tid] < 0) L.arow[tid] = L.arow[0];   // padding rows read a valid row
-  __syncthreads();
-  // activation scales: thread t moves row t%64, blocks t/64 and t/64 + 4 of
-  // each group, divided by 16 (zero for padding rows)
-  const int dm = tid & (MT - 1), dj = tid >> 6;
-  const float dlive = L.pair[dm] >= 0 ? 0.0625f : 0.0f;
-  const float *dsrc = a.actd + (int64_t)L.arow[dm] * nblk + dj;
-  float dx0 = 0.0f, dx1 = 0.0f;
-  if (resident) {
-    for (int g = 0; g < G; g++) {
-      stage_codes(a, L, g, g, NWV, wave, lane, nblk);
-      L.dx[g][dj][dm] = scale_pair(dlive * dsrc[8 * g]);
-      L.dx[g][dj + 4][dm] = scale_pair(dlive * dsrc[8 * g + 4]);
-    }
-  } else {
-    stage_codes(a, L, 0, 0, NWV, wave, lane, nblk);
-    dx0 = dsrc[0];
-    dx1 = dsrc[4];
-  }
 
-  // this lane's half of its weight row in slice s, and the step to the
-  // next group of 8 blocks
-  const int64_t rowbytes = (int64_t)nblk * Q4B;
-  const uint8_t *Wx = (expert < a.E ? a.w + (int64_t)expert * a.N * rowbytes : a.ws) + 72 * hh;
-  auto wrow = [&](int s) -> const uint8_t * {
-    int64_t grow;
+  // ---- direct loads: this lane's sources
+  // weights: the wave's 32 rows as 160 pieces of 16 bytes, piece i of row i / 5
+  constexpr int BB = SYM ? Q4SB : Q4B;
+  const uint32_t rowbytes = (uint32_t)nblk * BB;
+  const uint8_t *const W =
+      expert < a.E ? a.w + (int64_t)expert * a.N * (int64_t)rowbytes : a.ws;
+  const uint8_t *wsrc[3];
+#pragma unroll
+  for (int u = 0; u < 3; u++) {
+    const int i = min(64 * u + lane, 32 * WCH - 1);
+    const int r = i / WCH;
+    uint32_t grow;
     if (GATEUP) {
-      const int64_t col = (int64_t)s * 64 + 16 * wave + (r32 & 15);
-      grow = r32 < 16 ? col : a.I + col;
+      const uint32_t col = (uint32_t)slice * 64 + 16 * wave + (r & 15);
+      grow = r < 16 ? col : (uint32_t)a.I + col;
     } else {
       // a last slice past N (dense products) reads row N - 1 and stores nothing
-      grow = min((int64_t)s * WROWS + 32 * wave + r32, a.N - 1);
+      grow = min((uint32_t)slice * WROWS + 32 * wave + r, (uint32_t)a.N - 1);
     }
-    return Wx + grow * rowbytes;
+    wsrc[u] = W + (uint64_t)grow * rowbytes + 16 * (i - r * WCH);
+  }
+  // codes: 8 rows of 128 bytes per instruction, CPW of them per wave (a
+  // 16-row tile has two; waves 2 and 3 repeat them); scales: 16 bytes per
+  // row, a quarter of the rows per wave
+  constexpr int CPW = ROWS == 64 ? 2 : 1;
+  constexpr int PER = 3 + CPW + 1;                // direct loads of a wave per stage
+  const uint8_t *csrc[CPW];
+  int crow[CPW];
+#pragma unroll
+  for (int u = 0; u < CPW; u++) {
+    crow[u] = (8 * (CPW * wave + u)) % ROWS;
+    const int r = crow[u] + (lane >> 3);
+    csrc[u] = reinterpret_cast<const uint8_t *>(a.act) + (int64_t)arow[r] * nblk * 32 +
+              16 * ((lane & 7) ^ ((r >> 1) & 7));
+  }
+  constexpr int SPW = ROWS / 4;                   // scale rows per wave
+  const uint8_t *ssrc = reinterpret_cast<const uint8_t *>(a.actd) +
+                        (int64_t)arow[SPW * wave + (lane & (SPW - 1))] * nblk * 4;
+  __syncthreads();                                // the ring takes arow's place
+  auto load_stage = [&](int t) {
+    uint8_t *const slot = ring + (t % NS) * SLOT;
+    // a stage of Q4_0 is half a 144-byte group: bytes 0..79 or 64..143
+    const uint32_t o = SYM ? t * 80u : (t >> 1) * 144u + (t & 1) * 64u;
+    uint8_t *const dst = slot + wave * (32 * WCH * 16);
+    lds_dma16(wsrc[0] + o, dst);
+    lds_dma16(wsrc[1] + o, dst + 1024);
+    if (lane < 32 * WCH - 128) lds_dma16(wsrc[2] + o, dst + 2048);
+#pragma unroll
+    for (int u = 0; u < CPW; u++)
+      lds_dma16(csrc[u] + t * 128u, slot + SLOT_W + crow[u] * 128);
+    if (lane < SPW) lds_dma16(ssrc + t * 16u, slot + SLOT_W + ROWS * 128 + SPW * wave * 16);
   };
-  // this wave's weight-row scales of the current group: [block][row], rows
-  // padded to 36 so the two wave halves write distinct banks
-  float *const Lw = &L.dw[wave][0][0];
+#pragma unroll
+  for (int t = 0; t < NS - 1; t++)
+    if (t < S) load_stage(t);
+
+  // this lane's roles: 32-row halves: weight row and token l % 32, half hh of
+  // the block's elements; 16-row tiles: weight rows l % 16 and 16 + l % 16,
+  // token l % 16, quarter c of the elements
+  const int r32 = lane & 31, hh = lane >> 5;
+  const int t16 = lane & 15, c16 = lane >> 4;
+  float(*const Lw)[32] = L.dw[wave];
 
   float acc0[16], acc1[16];
 #pragma unroll
@@ -399,98 +357,103 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
   v16i c0;
 #pragma unroll
   for (int e = 0; e < 16; e++) c0[e] = BIAS;
+  const v4i c4 = v4i{BIAS, BIAS, BIAS, BIAS};
 
-  const int J = ns * G;
-  // group j with its weights in w; loads group j + 1 into wn (the last group
-  // reloads itself: no conditional loads into a register array)
-  auto step = [&](int j, const HW &w, HW &wn) {
-    const int sj = j / G, g = j - sj * G;
-    if (!resident) {
-      // buffer g&1 was last read in group g - 2, before the previous barrier
-      L.dx[g & 1][dj][dm] = scale_pair(dlive * dx0);
-      L.dx[g & 1][dj + 4][dm] = scale_pair(dlive * dx1);
-    }
-    if (!resident || j == 0) {
-      __builtin_amdgcn_s_waitcnt(0);              // codes, scales and weights have landed
-      __syncthreads();                            // ... for every wave
-    }
-    // next group's codes, then its weights.  The codes go first: the
-    // compiler cannot tell the direct loads into the other buffer from the
-    // reads of this one and waits for them before this group's products,
-    // so only loads issued after them stay in flight across the group.
-    if (!resident && g + 1 < G) {
-      stage_codes(a, L, g + 1, (g + 1) & 1, NWV, wave, lane, nblk);
-      dx0 = dsrc[8 * (g + 1)];
-      dx1 = dsrc[8 * (g + 1) + 4];
-    }
-    const int jn = j + 1 < J ? j + 1 : j;
-    const int sn = jn / G;
-    load_hw(wrow(s0 + sn) + (int64_t)(jn - sn * G) * (8 * Q4B), wn);
-    // this group's weight-row scales to the wave's table: blocks 4hh..4hh+3
+  for (int t = 0; t < S; t++) {
+    // stage t has landed (of what is younger, up to NS - 2 stages' loads may
+    // be under way), and every wave is done with stage t - 1, whose slot the
+    // next loads fill
+    if (NS > 2 && t + NS - 2 < S)
+      wait_barrier<(NS - 2) * PER>();
+    else if (NS > 3 && t + 1 < S)
+      wait_barrier<(NS > 3 ? PER : 0)>();
+    else
+      wait_barrier<0>();
+    if (t + NS - 1 < S) load_stage(t + NS - 1);
+    const uint8_t *slot = ring + (t % NS) * SLOT;
+    const uint32_t *wb =
+        reinterpret_cast<const uint32_t *>(slot + wave * (32 * WCH * 16)) + (SYM ? 0 : 2 * (t & 1));
+    const uint4 *ab = reinterpret_cast<const uint4 *>(slot + SLOT_W);
+    const float4 *db = reinterpret_cast<const float4 *>(slot + SLOT_W + ROWS * 128);
+    // the stage's weight-row scales to the wave's table: blocks 2hh, 2hh + 1
     // of row r32 (the wave's earlier reads of the table were issued before
     // these writes, and LDS runs one wave's accesses in order)
-#pragma unroll
-    for (int jj = 0; jj < 4; jj++) {
-      const uint32_t sd = hw_sdw(w, jj);
-      Lw[(4 * hh + jj) * DWS + r32] = f16_bits_to_f32((jj & 1) ? sd >> 16 : sd);
+    {
+      const uint32_t *wl = wb + r32 * WDW + (SYM ? 10 : 9) * hh;
+      Lw[2 * hh][r32] = wscale<SYM>(wl, 0);
+      Lw[2 * hh + 1][r32] = wscale<SYM>(wl, 1);
     }
     __builtin_amdgcn_wave_barrier();
-    const int buf = resident ? g : (g & 1);
-    const float2(*dxb)[MT] = L.dx[buf];
-    const uint4 *abuf = L.a[buf];
-    // each block's LDS operands are read one block ahead of its products
-    // (order 0, 4, 1, 5, 2, 6, 3, 7)
-    if constexpr (H16) {
-      const int t16 = lane & 15, c16 = lane >> 4;
-      const v4i c4 = v4i{BIAS, BIAS, BIAS, BIAS};
-      BlockIn16 nx = block_in16(abuf, Lw, dxb[0], 0, t16, c16);
+    if constexpr (KIND == T16) {
+      const uint32_t *wl = wb + t16 * WDW;
+      const float4 d = db[t16];
+      const float dx[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        v4i b0, b1;
-        uint32_t sd0, sd1;
-        pair_ops(w, jj, b0, b1, sd0, sd1);
-        BlockIn16 cur = nx;
-        nx = block_in16(abuf, Lw + (jj + 4) * DWS, dxb[jj + 4], jj + 4, t16, c16);
-        block16(acc0, cur, b0, c4);
-        cur = nx;
-        if (jj + 1 < 4) nx = block_in16(abuf, Lw + (jj + 1) * DWS, dxb[jj + 1], jj + 1, t16, c16);
-        block16(acc0, cur, b1, c4);
+      for (int j = 0; j < SB; j++) {
+        const long m0 = wcodes1<SYM>(wl, j, c16), m1 = wcodes1<SYM>(wl + 16 * WDW, j, c16);
+        const v2u *bp = reinterpret_cast<const v2u *>(
+            ab + t16 * 8 + ((2 * j + (c16 >> 1)) ^ ((t16 >> 1) & 7)));
+        const long b = __builtin_bit_cast(long, bp[c16 & 1]);
+        const v4f f0 = mm16(m0, b, c4), f1 = mm16(m1, b, c4);
+        const float4 w0 = *reinterpret_cast<const float4 *>(&Lw[j][4 * c16]);
+        const float4 w1 = *reinterpret_cast<const float4 *>(&Lw[j][16 + 4 * c16]);
+        const float nb = -BIASF * dx[j];
+        scale4<SYM>(acc0, f0[0], f0[1], f0[2], f0[3], dx[j], nb, w0);
+        scale4<SYM>(acc0 + 4, f1[0], f1[1], f1[2], f1[3], dx[j], nb, w1);
       }
     } else {
-      BlockIn nx = block_in<TWO, !SK>(abuf, Lw, dxb[0], 0, r32, hh);
+      const uint32_t *wl = wb + r32 * WDW;
+      const int sw = (r32 >> 1) & 7;              // rows r32 and r32 + 32 swizzle alike
+      const uint4 *a0 = ab + r32 * 8, *a1 = ab + (32 + r32) * 8;
+      const float4 d0 = db[r32];
+      const float4 d1 = KIND == T64 ? db[32 + r32] : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float dx0[4] = {d0.x, d0.y, d0.z, d0.w}, dx1[4] = {d1.x, d1.y, d1.z, d1.w};
+      // the scales of block j and the operands of block j + 1 are read behind
+      // block j's products; the latter land while block j is scaled
+      BlockIn in = block_in<SYM, KIND == T64>(wl, a0, a1, 0, hh, sw);
 #pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        v4i b0, b1;
-        uint32_t sd0, sd1;
-        pair_ops(w, jj, b0, b1, sd0, sd1);
-        BlockIn cur = nx;
-        nx = block_in<TWO, !SK>(abuf, Lw + (jj + 4) * DWS, dxb[jj + 4], jj + 4, r32, hh);
-        block<TWO, !SK>(acc0, acc1, cur, b0, c0, r32);
-        cur = nx;
-        if (jj + 1 < 4)
-          nx = block_in<TWO, !SK>(abuf, Lw + (jj + 1) * DWS, dxb[jj + 1], jj + 1, r32, hh);
-        block<TWO, !SK>(acc0, acc1, cur, b1, c0, r32);
+      for (int j = 0; j < SB; j++) {
+        const v4i wo = wcodes2<SYM>(in.r, j);
+        const v16f f0 = mm(wo, in.u0, c0);
+        v16f f1;
+        if (KIND == T64) f1 = mm(wo, in.u1, c0);
+        float4 dw[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+          dw[q] = *reinterpret_cast<const float4 *>(&Lw[j][8 * q + 4 * hh]);
+        if (j + 1 < SB) in = block_in<SYM, KIND == T64>(wl, a0, a1, j + 1, hh, sw);
+        __builtin_amdgcn_sched_barrier(0);
+        scale16<SYM>(acc0, f0, dx0[j], -BIASF * dx0[j], dw);
+        if (KIND == T64) scale16<SYM>(acc1, f1, dx1[j], -BIASF * dx1[j], dw);
       }
     }
-    if (g + 1 < G) return;
+  }
 
-    const int slice = s0 + sj;
+  // the ring becomes the h tile and the rows' pairs and combine weights
+  wait_barrier<0>();
+  float(*const hv)[HVS] = reinterpret_cast<float(*)[HVS]>(ring);
+  int *const Lpair = reinterpret_cast<int *>(ring + EPI_BYTES);
+  float *const Lpw = reinterpret_cast<float *>(ring + EPI_BYTES + 4 * MT);
+  if (tid < ROWS) {
+    const int p = row_pair(tid);
+    Lpair[tid] = p;
+    if (!GATEUP) Lpw[tid] = p >= 0 ? pair_weight(a, p) : 0.0f;
+  }
     if (GATEUP) {
-      __syncthreads();                            // the code buffers become the h tile
       // element e < 8 holds the gate sum and e + 8 the up sum of column
       // 16*wave + 8*(e/4) + 4*hh + e%4 for this lane's token (16-row tiles:
       // e < 4 gate and e + 4 up of column 16*wave + 4*(lane/16) + e of
       // token lane%16)
-      if constexpr (H16) {
+      if constexpr (KIND == T16) {
         const float *acc = acc0;
-        *reinterpret_cast<float4 *>(&L.hv[lane & 15][16 * wave + 4 * (lane >> 4)]) =
+        *reinterpret_cast<float4 *>(&hv[lane & 15][16 * wave + 4 * (lane >> 4)]) =
             make_float4(silu_f32(acc[0]) * acc[4], silu_f32(acc[1]) * acc[5],
                         silu_f32(acc[2]) * acc[6], silu_f32(acc[3]) * acc[7]);
       } else {
 #pragma unroll
-      for (int half = 0; half < (TWO ? 2 : 1); half++) {
+      for (int half = 0; half < (KIND == T64 ? 2 : 1); half++) {
         const float *acc = half ? acc1 : acc0;
-        float *hrow = &L.hv[32 * half + r32][16 * wave + 4 * hh];
+        float *hrow = &hv[32 * half + r32][16 * wave + 4 * hh];
 #pragma unroll
         for (int q = 0; q < 2; q++)
           *reinterpret_cast<float4 *>(hrow + 8 * q) =
@@ -504,157 +467,122 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
       // Q8_0 of each row's two 32-wide blocks: 8 lanes per block
       const int nbh = (int)(a.I / 32);
 #pragma unroll
-      for (int pass = 0; pass < 4; pass++) {
+      for (int pass = 0; pass < ROWS * 16 / MNT; pass++) {
         const int idx = pass * MNT + tid;
         const int rb = idx >> 3, jq = idx & 7, m = rb >> 1, cb = rb & 1;
-        const int p = L.pair[m];
+        const int p = Lpair[m];
         if (p >= 0) {                             // whole 8-lane groups agree
-          const float4 hv4 = *reinterpret_cast<const float4 *>(&L.hv[m][32 * cb + 4 * jq]);
+          const float4 hv4 = *reinterpret_cast<const float4 *>(&hv[m][32 * cb + 4 * jq]);
           const float v[4] = {hv4.x, hv4.y, hv4.z, hv4.w};
           uint32_t d16;
           const uint32_t packed = q8_0_block8(v, d16);
           const int bi = 2 * slice + cb;
           const int64_t blk = (int64_t)p * nbh + bi;
           store_q8_0_block8(a.hq + blk * Q8B, jq, packed, d16);
-          a.ha[blk * 8 + jq] = packed;
+          a.ha[blk * 8 + aligned_pos(jq)] = packed;
           if (jq == 0) a.hd[blk] = f16_bits_to_f32(d16);
           *reinterpret_cast<float4 *>(a.h + (int64_t)p * a.I + 32 * bi + 4 * jq) = hv4;
         }
       }
     } else {
-      // element 4q + i: output column slice*128 + 32*wave + 8q + 4hh + i
-      // (16-row tiles: element 4q + i of token lane%16, column slice*128 +
-      // 32*wave + 16q + 4*(lane/16) + i)
-      const bool vec = (a.N & 3) == 0;
-      if constexpr (H16) {
-        const int m = lane & 15;
-        const int p = L.pair[m];
-        const float pw = L.pw[m];
-        if (p >= 0) {
-          float *yrow = a.y + (int64_t)p * a.N;
-          const int64_t nb = (int64_t)slice * WROWS + 32 * wave + 4 * (lane >> 4);
+      __syncthreads();
+      // w * y of the tile through LDS, so that half a wave stores a whole row
+      // of 512 bytes instead of 32-byte pieces of 32 rows: element 4q + i is
+      // column 32*wave + 8q + 4hh + i of the slice (16-row tiles: of token
+      // lane%16, column 32*wave + 16q + 4*(lane/16) + i)
+      constexpr int YVS = WROWS + 4;
+      float *const yt = reinterpret_cast<float *>(ring);
+      static_assert(MT * YVS * 4 <= EPI_BYTES, "the output tile fits the epilogue");
+      if constexpr (KIND == T16) {
+        const float pw = Lpw[t16];
 #pragma unroll
-          for (int q = 0; q < 2; q++) {
-            const int64_t n = nb + 16 * q;
-            if (vec && n + 3 < a.N) {
-              *reinterpret_cast<float4 *>(yrow + n) =
-                  make_float4(pw * acc0[4 * q], pw * acc0[4 * q + 1], pw * acc0[4 * q + 2],
-                              pw * acc0[4 * q + 3]);
-            } else {
+        for (int q = 0; q < 2; q++)
+          *reinterpret_cast<float4 *>(yt + t16 * YVS + 32 * wave + 16 * q + 4 * c16) =
+              make_float4(pw * acc0[4 * q], pw * acc0[4 * q + 1], pw * acc0[4 * q + 2],
+                          pw * acc0[4 * q + 3]);
+      } else {
 #pragma unroll
-              for (int i = 0; i < 4; i++)
-                if (n + i < a.N) yrow[n + i] = pw * acc0[4 * q + i];
-            }
-          }
-        }
-      }
-      const int64_t n0 = (int64_t)slice * WROWS + 32 * wave + 4 * hh;
+        for (int half = 0; half < (KIND == T64 ? 2 : 1); half++) {
+          const float *acc = half ? acc1 : acc0;
+          const float pw = Lpw[32 * half + r32];
 #pragma unroll
-      for (int half = 0; half < (H16 ? 0 : (TWO ? 2 : 1)); half++) {
-        const float *acc = half ? acc1 : acc0;
-        const int m = 32 * half + r32;
-        const int p = L.pair[m];
-        const float pw = L.pw[m];
-        if (p < 0) continue;
-        float *yrow = a.y + (int64_t)p * a.N;
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const int64_t n = n0 + 8 * q;
-          if (vec && n + 3 < a.N) {
-            *reinterpret_cast<float4 *>(yrow + n) =
+          for (int q = 0; q < 4; q++)
+            *reinterpret_cast<float4 *>(yt + (32 * half + r32) * YVS + 32 * wave + 8 * q + 4 * hh) =
                 make_float4(pw * acc[4 * q], pw * acc[4 * q + 1], pw * acc[4 * q + 2],
                             pw * acc[4 * q + 3]);
-          } else {
+        }
+      }
+      __syncthreads();
+      const bool vec = (a.N & 3) == 0;
+      const int64_t n = (int64_t)slice * WROWS + 4 * r32;
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-              if (n + i < a.N) yrow[n + i] = pw * acc[4 * q + i];
-          }
+      for (int u = 0; u < ROWS / 8; u++) {
+        const int m = 8 * u + 2 * wave + hh, p = Lpair[m];
+        if (p < 0 || n >= a.N) continue;
+        const float4 v = *reinterpret_cast<const float4 *>(yt + m * YVS + 4 * r32);
+        float *yp = a.y + (int64_t)p * a.N + n;
+        if (vec) {
+          *reinterpret_cast<float4 *>(yp) = v;
+        } else {
+          yp[0] = v.x;
+          if (n + 1 < a.N) yp[1] = v.y;
+          if (n + 2 < a.N) yp[2] = v.z;
+          if (n + 3 < a.N) yp[3] = v.w;
         }
       }
     }
-#pragma unroll
-    for (int e = 0; e < 16; e++) { acc0[e] = 0.0f; acc1[e] = 0.0f; }
-  };
-
-  HW wa, wb;
-  load_hw(wrow(s0), wa);
-  for (int j = 0; j < J; j += 2) {
-    step(j, wa, wb);
-    if (j + 1 < J) step(j + 1, wb, wa);
-  }
 }
 
-template <bool GATEUP, bool SHORT>
+template <bool GATEUP, bool SYM>
 __device__ __forceinline__ void mfma_body(const MArgs &a, MLds &L) {
-  // Work items are (tile, chunk), chunk = a run of spw slices.  Workgroup b
-  // runs on XCD b % 8 and is the (b / 8)-th item there.  Each XCD takes an
+  // Work items are (tile, slice).  Workgroup b runs on XCD b % 8 and is the
+  // (b / 8)-th item there.  Each XCD takes an
   // even share of the long tiles (more than 32 rows), then an even share of
   // the short ones, each share a contiguous run of tiles (neighbouring tiles
-  // of one expert share its weights in that XCD's L2), and all chunks of a
+  // of one expert share its weights in that XCD's L2), and all slices of a
   // tile in a row (they share the tile's codes).
   const int nsl = (int)(GATEUP ? a.I / 64 : (a.N + WROWS - 1) / WROWS);
-  const int nch = (nsl + a.spw - 1) / a.spw;
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
-  int expert, pos, rows, s0;
+  int expert, pos, rows, slice;
   if (a.M) {
-    // Dense products: the items in chunk-major order (all 64-row tiles of
-    // the activations for one chunk of weight rows in a row), XCD x taking
-    // the x-th of 8 even contiguous runs: the tiles of one chunk share its
+    // Dense products: the items in slice-major order (all 64-row tiles of
+    // the activations for one slice of weight rows in a row), XCD x taking
+    // the x-th of 8 even contiguous runs: the tiles of one slice share its
     // weights in that XCD's L2, and every XCD streams its own part of the
     // weights, so a handful of tiles still spreads over all 8.
     const int ntl = (int)((a.M + a.tr - 1) / a.tr);
-    const int tot = nch * ntl;
+    const int tot = nsl * ntl;
     const int i0 = x * tot / 8, nx = (x + 1) * tot / 8 - i0;
     if (q >= nx) return;
-    const int c = (i0 + q) / ntl, tile = (i0 + q) - c * ntl;
-    s0 = c * a.spw;
+    slice = (i0 + q) / ntl;
+    const int tile = (i0 + q) - slice * ntl;
     expert = 0;                  // E = 0: the weights are ws
     pos = tile * a.tr;
     rows = (int)min((int64_t)a.tr, a.M - pos);
   } else {
-    const int ch = q % nch, qt = q / nch;
+    const int qt = q / nsl;
+    slice = q - qt * nsl;
     const int ntiles = ((CInt *)a.meta)[2], nlong = ((CInt *)a.meta)[4];   // META_NTILES, META_NLONG
     const int l0 = x * nlong / 8, nl = (x + 1) * nlong / 8 - l0;
     const int nshort = ntiles - nlong;
     const int s0t = nlong + x * nshort / 8, ns_ = nlong + (x + 1) * nshort / 8 - s0t;
     if (qt >= nl + ns_) return;
     const int tile = qt < nl ? l0 + qt : s0t + (qt - nl);
-    s0 = ch * a.spw;
     CInt *tp = (CInt *)a.tiles + 4 * tile;
     expert = tp[0]; pos = tp[1]; rows = tp[2];
   }
-  const int ns = min(a.spw, nsl - s0);
-  if (a.K <= 512) {
-    if (!SHORT && rows > 32)
-      mfma_tile<GATEUP, true, true, SHORT>(a, L, expert, pos, rows, s0, ns);
-    else if (rows > 16)
-      mfma_tile<GATEUP, false, true, SHORT>(a, L, expert, pos, rows, s0, ns);
-    else
-      mfma_tile<GATEUP, false, true, SHORT, true>(a, L, expert, pos, rows, s0, ns);
-  } else {
-    if (!SHORT && rows > 32)
-      mfma_tile<GATEUP, true, false, SHORT>(a, L, expert, pos, rows, s0, ns);
-    else if (rows > 16)
-      mfma_tile<GATEUP, false, false, SHORT>(a, L, expert, pos, rows, s0, ns);
-    else
-      mfma_tile<GATEUP, false, false, SHORT, true>(a, L, expert, pos, rows, s0, ns);
-  }
+  if (rows > 32)
+    mfma_tile<GATEUP, T64, SYM>(a, L, expert, pos, rows, slice);
+  else if (rows > 16)
+    mfma_tile<GATEUP, T32, SYM>(a, L, expert, pos, rows, slice);
+  else
+    mfma_tile<GATEUP, T16, SYM>(a, L, expert, pos, rows, slice);
 }
 
-// Tiles of up to 64 rows: two waves per SIMD (the 64-row tile's two sets of
-// sums and products need about 200 registers a lane; at three waves the
-// compiler spills inside the block loop).
-template <bool GATEUP>
-__global__ __launch_bounds__(MNT) __attribute__((amdgpu_waves_per_eu(2))) void mfma_kernel(MArgs a) {
+template <bool GATEUP, bool SYM>
+__global__ __launch_bounds__(MNT) __attribute__((amdgpu_waves_per_eu(3))) void mfma_kernel(MArgs a) {
   __shared__ MLds L;
-  mfma_body<GATEUP, false>(a, L);
-}
-
-// Dense products of at most 32 rows (every tile short): one set of sums,
-// three waves per SIMD to keep more weight bytes in flight.
-__global__ __launch_bounds__(MNT) __attribute__((amdgpu_waves_per_eu(3))) void mfma_short_kernel(MArgs a) {
-  __shared__ MLds L;
-  mfma_body<false, true>(a, L);
+  mfma_body<GATEUP, SYM>(a, L);
 }
 
 }  // namespace
@@ -670,27 +598,22 @@ int mfma_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint32_t *xa, c
   a.meta = meta; a.perm = perm; a.tiles = tiles;
   a.h = h; a.hq = hq; a.ha = ha; a.hd = hd;
   a.T = T; a.k = k; a.E = E; a.N = 2 * I; a.K = H; a.I = I;
-  a.spw = 1;                       // the h tile reuses the code buffers
   // an XCD takes at most ceil(long/8) + ceil(short/8) <= ceil(maxtiles/8) + 1 tiles
-  mfma_kernel<true><<<dim3((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * (I / 64))), dim3(MNT), 0, s>>>(a);
+  mfma_kernel<true, false><<<dim3((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * (I / 64))), dim3(MNT), 0, s>>>(a);
   return check_launch();
 }
 
 int mfma_down(const uint8_t *w_d, const uint8_t *ws_d, const uint32_t *ha, const float *hd,
               const int32_t *meta, const int32_t *perm, const int4 *tiles, const float *topk_w,
               const float *shared_w, float *y, int64_t maxtiles, int64_t T, int64_t H, int64_t I,
-              int64_t E, int64_t k, bool few, hipStream_t s) {
+              int64_t E, int64_t k, hipStream_t s) {
   MArgs a{};
   a.w = w_d; a.ws = ws_d; a.act = ha; a.actd = hd;
   a.meta = meta; a.perm = perm; a.tiles = tiles;
   a.topk_w = topk_w; a.shared_w = shared_w; a.y = y;
   a.T = T; a.k = k; a.E = E; a.N = H; a.K = I; a.I = I;
   const int64_t nsl = H / WROWS;
-  // few tiles: one slice per workgroup, so the slices spread over more
-  // compute units
-  a.spw = I <= 512 && !few ? (int)std::min<int64_t>(SPW_MAX, nsl) : 1;
-  const int64_t nch = (nsl + a.spw - 1) / a.spw;
-  mfma_kernel<false><<<dim3((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * nch)), dim3(MNT), 0, s>>>(a);
+  mfma_kernel<false, false><<<dim3((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * nsl)), dim3(MNT), 0, s>>>(a);
   return check_launch();
 }
 
@@ -703,15 +626,10 @@ int mfma_dense(const uint8_t *w, const uint32_t *act, const float *actd, float *
   a.T = 0; a.k = 0; a.E = 0; a.N = N; a.K = K; a.I = K; a.M = M;
   const int64_t nsl = (N + WROWS - 1) / WROWS;
   a.tr = MT;
-  a.spw = K <= 512 ? (int)std::min<int64_t>(SPW_MAX, nsl) : 1;
-  const int64_t nch = (nsl + a.spw - 1) / a.spw;
   const int64_t ntiles = (M + a.tr - 1) / a.tr;
-  const int64_t grid = 8 * ((nch * ntiles + 7) / 8);    // an XCD takes at most ceil(items/8)
+  const int64_t grid = 8 * ((nsl * ntiles + 7) / 8);    // an XCD takes at most ceil(items/8)
   if (grid >= ((int64_t)1 << 31)) return W4A8_ERANGE;
-  if (M <= MT / 2)
-    mfma_short_kernel<<<dim3((unsigned)grid), dim3(MNT), 0, s>>>(a);
-  else
-    mfma_kernel<false><<<dim3((unsigned)grid), dim3(MNT), 0, s>>>(a);
+  mfma_kernel<false, false><<<dim3((unsigned)grid), dim3(MNT), 0, s>>>(a);
   return check_launch();
 }
 

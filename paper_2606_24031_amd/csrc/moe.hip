@@ -46,7 +46,7 @@ int mfma_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint32_t *xa, c
 int mfma_down(const uint8_t *w_d, const uint8_t *ws_d, const uint32_t *ha, const float *hd,
               const int32_t *meta, const int32_t *perm, const int4 *tiles, const float *topk_w,
               const float *shared_w, float *y, int64_t maxtiles, int64_t T, int64_t H, int64_t I,
-              int64_t E, int64_t k, bool few, hipStream_t s);
+              int64_t E, int64_t k, hipStream_t s);
 size_t decode_sync_words(int64_t H);
 size_t decode_xfer_words();
 bool decode_supported(int64_t H, int64_t I, int64_t k);
@@ -871,8 +871,7 @@ int moe_forward_impl(const float *hidden, DecodeNorm norm, const int32_t *ids,
   ra.T = (int)T; ra.k = (int)k; ra.E = (int)E; ra.has_shared = has_shared; ra.ms = ms;
   // 64-row tiles, unless the pairs fill so few of them that most compute
   // units would get no gate/up workgroup (one expert over a prompt, a short
-  // prompt's shared group): then 32-row tiles, and one down slice per
-  // workgroup
+  // prompt's shared group): then 32-row tiles
   const int64_t est64 = (std::max<int64_t>((T * k + MC - 1) / MC, std::min<int64_t>(E, T * k)) +
                          (has_shared ? (T + MC - 1) / MC : 0)) * (I / 64);
   ra.mc = est64 < 2 * std::max(1, device_cus()) ? MC_FEW : MC;
@@ -940,7 +939,7 @@ int moe_forward_impl(const float *hidden, DecodeNorm norm, const int32_t *ids,
                                  maxchunks, T, H, I, E, k, s)) != W4A8_OK)
     return rc;
   if (tiles && (rc = mfma_down(w_d, ws_d, ha, hd, ra.meta, ra.perm, ra.tiles, topk_w, shared_w,
-                               y, gtiles, T, H, I, E, k, ra.mc == MC_FEW, s)) != W4A8_OK)
+                               y, gtiles, T, H, I, E, k, s)) != W4A8_OK)
     return rc;
 
   const int64_t n4 = T * (H / 4);

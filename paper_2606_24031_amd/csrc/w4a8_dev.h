@@ -304,10 +304,15 @@ __device__ __forceinline__ void store_q8_0_block8(uint8_t *blk, int j, uint32_t 
   if (j == 0) *reinterpret_cast<uint16_t *>(blk) = (uint16_t)d16;
 }
 
+// Position of a block's code dword j (elements 4j..4j+3) in the aligned form
+// the matrix-core tiles read: dwords 0 4 1 5 2 6 3 7, so that the elements
+// which share a Q4_0 payload dword are neighbours.
+__host__ __device__ constexpr int aligned_pos(int j) { return 2 * (j & 3) + (j >> 2); }
+
 // Q8_0 of one 32-element block of x by 8 lanes (thread tid: block tid / 8,
 // elements 4 (tid % 8) .. + 3): the 34-byte block, and when the pointers are
 // set its nibble-split form (xs, rows of nbrow blocks, see split_blk) and its
-// 32 codes on a 32-byte boundary with the fp32 scale (xa, xd).  Lanes past
+// 32 codes on a 32-byte boundary (see aligned_pos) with the fp32 scale (xa, xd).  Lanes past
 // nblocks take part in the exchanges and store nothing.  q8_0_lane_vals
 // takes the lane's four values already in registers (elements 4j..4j+3 of
 // block blk; live: the block exists); q8_0_lane loads them from x.
@@ -332,7 +337,7 @@ __device__ __forceinline__ void q8_0_lane_vals(const float v[4], uint8_t *__rest
     }
   }
   if (xa && live) {
-    xa[blk * 8 + j] = packed;
+    xa[blk * 8 + aligned_pos(j)] = packed;
     if (j == 0) xd[blk] = f16_bits_to_f32(d16);
   }
 }

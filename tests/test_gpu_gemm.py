@@ -36,13 +36,30 @@ def _rows_check(y, w, xq, N, K, rows, cols=None):
 # sixteen full); M = 129 and K = 4096: the MFMA tiles (33 one tile, both
 # 32-row halves; 64 and 65 a full tile, then a 1-row tile; 96 a full and a
 # 32-row tile; 2-32 the 32-row tiles of a few rows).  N: ragged past a
-# 128-row slice; K: 512 (codes resident, several slices per workgroup), 768
-# (three staged groups), 2048, 4096.
+# 128-row slice; K: 256 to 4096 (2 to 32 stages of the tiles).
 @pytest.mark.parametrize("M", [2, 8, 17, 32, 33, 64, 65, 96, 128, 129])
 @pytest.mark.parametrize("N,K", [(1000, 2048), (4096, 512), (333, 768), (40, 256), (300, 4096)])
 def test_gemm_matches_oracle(M, N, K):
     print(f"gemm M={M} N={N} K={K}", flush=True)
     g = synth.rng(10 * M + N + K)
+    w = synth.q4_0_random_blocks(g, N, K).reshape(N, -1)
+    xq = oracle.q8_0_quantize(synth.normal_f32(g, (M, K))).reshape(M, -1)
+    y = w4.q4q8_gemm(dev(w), dev(xq), M, N, K).cpu().numpy()
+    _rows_check(y, w, xq, N, K, range(M))
+
+
+# The matrix-core tiles' rings: a last tile of 1, 16 (the 16-row form), 17,
+# 32, 33 and 64 rows behind two full ones, over two and four stages of four
+# blocks (fewer than and as many as the ring's slots) and 18 (M <= 128 is on
+# the tiles there: K > 2048), and output rows of 131 (unaligned) and 260
+# columns (a slice of 4).
+@pytest.mark.parametrize("M", [129, 144, 145, 160, 161, 192])
+@pytest.mark.parametrize("N,K", [(131, 256), (260, 512), (131, 2304)])
+def test_gemm_tile_ring_edges(M, N, K):
+    print(f"gemm ring M={M} N={N} K={K}", flush=True)
+    M = M - 128 if K > 2048 else M
+    M = max(M, 2)                                  # one row is the GEMV
+    g = synth.rng(3 * M + N + K)
     w = synth.q4_0_random_blocks(g, N, K).reshape(N, -1)
     xq = oracle.q8_0_quantize(synth.normal_f32(g, (M, K))).reshape(M, -1)
     y = w4.q4q8_gemm(dev(w), dev(xq), M, N, K).cpu().numpy()
