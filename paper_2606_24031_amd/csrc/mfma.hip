@@ -474,13 +474,12 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
         if (p >= 0) {                             // whole 8-lane groups agree
           const float4 hv4 = *reinterpret_cast<const float4 *>(&hv[m][32 * cb + 4 * jq]);
           const float v[4] = {hv4.x, hv4.y, hv4.z, hv4.w};
-          uint32_t d16;
-          const uint32_t packed = q8_0_block8(v, d16);
           const int bi = 2 * slice + cb;
           const int64_t blk = (int64_t)p * nbh + bi;
-          store_q8_0_block8(a.hq + blk * Q8B, jq, packed, d16);
+          float d;
+          const uint32_t packed = quantize_block8<SYM>(v, a.hq, blk, jq, true, d);
           a.ha[blk * 8 + aligned_pos(jq)] = packed;
-          if (jq == 0) a.hd[blk] = f16_bits_to_f32(d16);
+          if (jq == 0) a.hd[blk] = d;
           *reinterpret_cast<float4 *>(a.h + (int64_t)p * a.I + 32 * bi + 4 * jq) = hv4;
         }
       }
@@ -592,28 +591,36 @@ int mfma_tile_rows() { return MT; }
 int mfma_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint32_t *xa, const float *xd,
                 const int32_t *meta, const int32_t *perm, const int4 *tiles, float *h,
                 uint8_t *hq, uint32_t *ha, float *hd, int64_t maxtiles, int64_t T, int64_t H,
-                int64_t I, int64_t E, int64_t k, hipStream_t s) {
+                int64_t I, int64_t E, int64_t k, bool sym, hipStream_t s) {
   MArgs a{};
   a.w = w_gu; a.ws = ws_gu; a.act = xa; a.actd = xd;
   a.meta = meta; a.perm = perm; a.tiles = tiles;
   a.h = h; a.hq = hq; a.ha = ha; a.hd = hd;
   a.T = T; a.k = k; a.E = E; a.N = 2 * I; a.K = H; a.I = I;
   // an XCD takes at most ceil(long/8) + ceil(short/8) <= ceil(maxtiles/8) + 1 tiles
-  mfma_kernel<true, false><<<dim3((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * (I / 64))), dim3(MNT), 0, s>>>(a);
+  const dim3 grid((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * (I / 64)));
+  if (sym)
+    mfma_kernel<true, true><<<grid, dim3(MNT), 0, s>>>(a);
+  else
+    mfma_kernel<true, false><<<grid, dim3(MNT), 0, s>>>(a);
   return check_launch();
 }
 
 int mfma_down(const uint8_t *w_d, const uint8_t *ws_d, const uint32_t *ha, const float *hd,
               const int32_t *meta, const int32_t *perm, const int4 *tiles, const float *topk_w,
               const float *shared_w, float *y, int64_t maxtiles, int64_t T, int64_t H, int64_t I,
-              int64_t E, int64_t k, hipStream_t s) {
+              int64_t E, int64_t k, bool sym, hipStream_t s) {
   MArgs a{};
   a.w = w_d; a.ws = ws_d; a.act = ha; a.actd = hd;
   a.meta = meta; a.perm = perm; a.tiles = tiles;
   a.topk_w = topk_w; a.shared_w = shared_w; a.y = y;
   a.T = T; a.k = k; a.E = E; a.N = H; a.K = I; a.I = I;
   const int64_t nsl = H / WROWS;
-  mfma_kernel<false, false><<<dim3((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * nsl)), dim3(MNT), 0, s>>>(a);
+  const dim3 grid((unsigned)(8 * ((maxtiles + 7) / 8 + 1) * nsl));
+  if (sym)
+    mfma_kernel<false, true><<<grid, dim3(MNT), 0, s>>>(a);
+  else
+    mfma_kernel<false, false><<<grid, dim3(MNT), 0, s>>>(a);
   return check_launch();
 }
 

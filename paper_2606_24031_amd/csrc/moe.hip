@@ -33,20 +33,20 @@ int64_t small_max_chunks(int64_t T, int64_t E, int64_t k, int has_shared);
 int small_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint8_t *xs,
                  const int32_t *meta, const int32_t *perm, const int4 *chunks, float *h,
                  uint8_t *hq, uint8_t *hs, int64_t maxchunks, int64_t T, int64_t H, int64_t I,
-                 int64_t E, int64_t k, hipStream_t s);
+                 int64_t E, int64_t k, bool sym, hipStream_t s);
 int small_down(const uint8_t *w_d, const uint8_t *ws_d, const uint8_t *hs, const int32_t *meta,
                const int32_t *perm, const int4 *chunks, const float *topk_w,
                const float *shared_w, float *y, int64_t maxchunks, int64_t T, int64_t H,
-               int64_t I, int64_t E, int64_t k, hipStream_t s);
+               int64_t I, int64_t E, int64_t k, bool sym, hipStream_t s);
 int mfma_tile_rows();
 int mfma_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint32_t *xa, const float *xd,
                 const int32_t *meta, const int32_t *perm, const int4 *tiles, float *h,
                 uint8_t *hq, uint32_t *ha, float *hd, int64_t maxtiles, int64_t T, int64_t H,
-                int64_t I, int64_t E, int64_t k, hipStream_t s);
+                int64_t I, int64_t E, int64_t k, bool sym, hipStream_t s);
 int mfma_down(const uint8_t *w_d, const uint8_t *ws_d, const uint32_t *ha, const float *hd,
               const int32_t *meta, const int32_t *perm, const int4 *tiles, const float *topk_w,
               const float *shared_w, float *y, int64_t maxtiles, int64_t T, int64_t H, int64_t I,
-              int64_t E, int64_t k, hipStream_t s);
+              int64_t E, int64_t k, bool sym, hipStream_t s);
 size_t decode_sync_words(int64_t H);
 size_t decode_xfer_words();
 bool decode_supported(int64_t H, int64_t I, int64_t k);
@@ -99,11 +99,16 @@ struct Layout {
 constexpr int64_t SMALL_T_MAX = 128;
 inline int small_rows(int64_t T) { return T <= SMALL_T_MAX ? (int)SMALL_T_MAX : 0; }
 
+// Bound on a call's row tiles, at the smaller tile size.
+int64_t max_tiles(int64_t T, int64_t E, int64_t k) {
+  return (T * k + MC_FEW - 1) / MC_FEW + std::min<int64_t>(E, T * k) + (T + MC_FEW - 1) / MC_FEW + 1;
+}
+
 // Region sizes depend only on (T, H, I, E, k).
 Layout make_layout(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
   Layout L;
   const int64_t P = T * k + T;
-  L.maxtiles = (T * k + MC_FEW - 1) / MC_FEW + std::min<int64_t>(E, T * k) + (T + MC_FEW - 1) / MC_FEW + 1;
+  L.maxtiles = max_tiles(T, E, k);
   size_t off = 0;
   L.meta = off;   off += 256;
   L.sync = off;   off += up256(sizeof(uint32_t) * decode_sync_words(H));
@@ -743,7 +748,7 @@ __device__ void norm_q8_rows(const Q8Args &q, int64_t wg) {
     xn[0] = v.x * r * g.x; xn[1] = v.y * r * g.y; xn[2] = v.z * r * g.z; xn[3] = v.w * r * g.w;
     reinterpret_cast<float4 *>(q.xn)[row * h4 + c] = make_float4(xn[0], xn[1], xn[2], xn[3]);
   }
-  q8_0_lane_vals(xn, q.xq, q.xs, q.xa, q.xd, q.nbrow, row * q.nbrow + (c >> 3), c & 7, live);
+  q8_lane_vals<false>(xn, q.xq, q.xs, q.xa, q.xd, q.nbrow, row * q.nbrow + (c >> 3), c & 7, live);
 }
 
 // Stages 1 and 2 in one launch (they are independent): the first `nroute`
@@ -751,7 +756,7 @@ __device__ void norm_q8_rows(const Q8Args &q, int64_t wg) {
 // slice of at most ROUTE_T pairs), or the ranks of one slice each (MODE 2,
 // finished by route_finish) -- the others quantize the hidden rows, ROUTE_T /
 // 8 blocks each.
-template <int MODE>
+template <int MODE, bool SYM>
 __global__ __launch_bounds__(ROUTE_T) void prep_kernel(RouteArgs a, Q8Args q, int nroute) {
   if ((int)blockIdx.x < nroute) {
     if (MODE >= 2)
@@ -760,11 +765,11 @@ __global__ __launch_bounds__(ROUTE_T) void prep_kernel(RouteArgs a, Q8Args q, in
       route_body<MODE>(a);
     return;
   }
-  if (q.norm_rows)
+  if (!SYM && q.norm_rows)
     norm_q8_rows(q, (int64_t)(blockIdx.x - nroute));
   else
-    q8_0_lane(q.x, q.xq, q.xs, q.xa, q.xd, q.nblocks, q.nbrow,
-              (int64_t)(blockIdx.x - nroute) * ROUTE_T + threadIdx.x);
+    q8_lane<SYM>(q.x, q.xq, q.xs, q.xa, q.xd, q.nblocks, q.nbrow,
+                 (int64_t)(blockIdx.x - nroute) * ROUTE_T + threadIdx.x);
 }
 
 // out[t] = sum_j y[t*k + j] (slots in order, skipped slots left out) + y[T*k + t].
@@ -805,47 +810,48 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
 
 }  // namespace
 
-int moe_forward_impl(const float *hidden, DecodeNorm norm, const int32_t *ids,
-                     const float *topk_w, const float *shared_w, const uint8_t *w_gu,
-                     const uint8_t *w_d,
-                     const uint8_t *ws_gu, const uint8_t *ws_d, float *out, int64_t T, int64_t H,
-                     int64_t I, int64_t E, int64_t k, uint8_t *ws, size_t ws_bytes,
-                     hipStream_t s) {
-  const Layout L = make_layout(T, H, I, E, k);
+namespace {
+
+// Where the grouped layer keeps its intermediate results.
+struct GroupedWs {
+  int32_t *meta, *perm, *count, *rank, *hist;
+  int4 *groups, *tiles, *chunks;
+  uint8_t *xq;              // quantized hidden rows (34- or 36-byte blocks)
+  float *h;
+  uint8_t *hq;
+  float *y;
+  uint8_t *xs, *hs;         // nibble-split copies (VALU kernels)
+  uint32_t *xa, *ha;        // aligned codes (matrix-core tiles)
+  float *xd, *hd;           // ... and scales
+};
+
+template <int MODE>
+void launch_prep(unsigned nroute, unsigned nq, size_t lds, bool sym, const RouteArgs &ra,
+                 const Q8Args &qa, hipStream_t s) {
+  if (sym)
+    prep_kernel<MODE, true><<<dim3(nroute + nq), dim3(ROUTE_T), lds, s>>>(ra, qa, (int)nroute);
+  else
+    prep_kernel<MODE, false><<<dim3(nroute + nq), dim3(ROUTE_T), lds, s>>>(ra, qa, (int)nroute);
+}
+
+// The grouped layer (T > 1): route and quantize, gate/up, down, combine.  sym:
+// the fp32-scale format (weights Q4_SYM, activations Q8_F32), no norm.
+int grouped_forward(const GroupedWs &R, const float *hidden, const DecodeNorm &norm,
+                    bool fold_norm, const int32_t *ids, const float *topk_w,
+                    const float *shared_w, const uint8_t *w_gu, const uint8_t *w_d,
+                    const uint8_t *ws_gu, const uint8_t *ws_d, float *out, int64_t T, int64_t H,
+                    int64_t I, int64_t E, int64_t k, bool sym, hipStream_t s) {
   const int has_shared = ws_gu != nullptr;
   int rc;
-  if (norm.gamma) norm.xn = reinterpret_cast<float *>(ws + L.xn);
-
-  // One token: the whole layer in a single launch, the residual RMSNorm
-  // included (see decode.hip).
-  if (T == 1 && decode_supported(H, I, k))
-    return decode_forward(hidden, norm, nullptr, ids, topk_w, shared_w, w_gu, w_d, ws_gu, ws_d, out, H, I,
-                          E, k,
-                          reinterpret_cast<uint32_t *>(ws + L.sync),
-                          reinterpret_cast<uint32_t *>(ws + L.xfer), ws + L.xq,
-                          reinterpret_cast<float *>(ws + L.h), ws + L.hq, s);
-
-  // the pre-norm residual step: inside the quantizing workgroups of the
-  // prep launch when a row fits one of them, else a launch of its own
-  const bool fold_norm = norm.gamma && H / 4 <= ROUTE_T;
-  if (norm.gamma && !fold_norm) {
-    if ((rc = launch_rmsnorm(hidden, norm.resid, norm.gamma, norm.x_out, norm.xn, T, H, norm.eps,
-                             s)) != W4A8_OK)
-      return rc;
-    hidden = norm.xn;
-  }
   const int ms = small_supported(H, I) ? small_rows(T) : 0;
   // with ms >= T every group (at most T rows) is small: no MFMA tiles
   const bool tiles = ms < T;
-  uint8_t *xs = ws + L.xs;
-  uint8_t *hs = ws + L.hs;
-  uint32_t *xa = reinterpret_cast<uint32_t *>(ws + L.xa);
-  uint32_t *ha = reinterpret_cast<uint32_t *>(ws + L.ha);
-  float *xd = reinterpret_cast<float *>(ws + L.xd);
-  float *hd = reinterpret_cast<float *>(ws + L.hd);
+  uint8_t *const xs = R.xs, *const hs = R.hs, *const hq = R.hq;
+  uint32_t *const xa = R.xa, *const ha = R.ha;
+  float *const xd = R.xd, *const hd = R.hd, *const h = R.h, *const y = R.y;
   Q8Args qa;
   qa.x = hidden;
-  qa.xq = ws + L.xq;
+  qa.xq = R.xq;
   qa.xs = ms > 0 ? xs : nullptr;
   qa.xa = tiles ? xa : nullptr;
   qa.xd = xd;
@@ -860,14 +866,14 @@ int moe_forward_impl(const float *hidden, DecodeNorm norm, const int32_t *ids,
 
   RouteArgs ra;
   ra.ids = ids;
-  ra.meta = reinterpret_cast<int32_t *>(ws + L.meta);
-  ra.perm = reinterpret_cast<int32_t *>(ws + L.perm);
-  ra.count = reinterpret_cast<int32_t *>(ws + L.count);
-  ra.rank = reinterpret_cast<int32_t *>(ws + L.rank);
-  ra.groups = reinterpret_cast<int4 *>(ws + L.groups);
-  ra.tiles = reinterpret_cast<int4 *>(ws + L.tiles);
-  ra.chunks = reinterpret_cast<int4 *>(ws + L.chunks);
-  ra.hist_g = reinterpret_cast<int32_t *>(ws + L.hist);
+  ra.meta = R.meta;
+  ra.perm = R.perm;
+  ra.count = R.count;
+  ra.rank = R.rank;
+  ra.groups = R.groups;
+  ra.tiles = R.tiles;
+  ra.chunks = R.chunks;
+  ra.hist_g = R.hist;
   ra.T = (int)T; ra.k = (int)k; ra.E = (int)E; ra.has_shared = has_shared; ra.ms = ms;
   // 64-row tiles, unless the pairs fill so few of them that most compute
   // units would get no gate/up workgroup (one expert over a prompt, a short
@@ -898,9 +904,9 @@ int moe_forward_impl(const float *hidden, DecodeNorm norm, const int32_t *ids,
     ra.tpe = (int)std::max<int64_t>(1, std::min<int64_t>(64, ROUTE_T / e2));
     const size_t lds1 = sizeof(int) * 16 * (size_t)E;
     if (nslice == 1) {
-      prep_kernel<3><<<dim3(1 + nq), dim3(ROUTE_T), lds1, s>>>(ra, qa, 1);
+      launch_prep<3>(1, nq, lds1, sym, ra, qa, s);
     } else {
-      prep_kernel<2><<<dim3((unsigned)nslice + nq), dim3(ROUTE_T), lds1, s>>>(ra, qa, (int)nslice);
+      launch_prep<2>((unsigned)nslice, nq, lds1, sym, ra, qa, s);
       if ((rc = check_launch()) != W4A8_OK) return rc;
       route_finish_kernel<<<dim3((unsigned)nslice + 1), dim3(ROUTE_T),
                             sizeof(int) * 4 * (size_t)(E + 1), s>>>(ra);
@@ -918,34 +924,143 @@ int moe_forward_impl(const float *hidden, DecodeNorm norm, const int32_t *ids,
     const size_t lds = sizeof(int) * std::max<size_t>((size_t)E * ra.nseg,
                                                       (ra.stage ? Pr + T : 0) + 3 * (E + 1));
     if (reg)
-      prep_kernel<1><<<dim3(1 + nq), dim3(ROUTE_T), lds, s>>>(ra, qa, 1);
+      launch_prep<1>(1, nq, lds, sym, ra, qa, s);
     else
-      prep_kernel<0><<<dim3(1 + nq), dim3(ROUTE_T), lds, s>>>(ra, qa, 1);
+      launch_prep<0>(1, nq, lds, sym, ra, qa, s);
   }
   if ((rc = check_launch()) != W4A8_OK) return rc;
 
-  uint8_t *hq = ws + L.hq;
-  float *h = reinterpret_cast<float *>(ws + L.h);
-  float *y = reinterpret_cast<float *>(ws + L.y);
   // launch bound on the small chunks (every group small when there are any)
   const int64_t maxchunks = small_max_chunks(T, E, k, has_shared);
   if (ms > 0 && (rc = small_gateup(w_gu, ws_gu, xs, ra.meta, ra.perm, ra.chunks, h, hq, hs,
-                                   maxchunks, T, H, I, E, k, s)) != W4A8_OK)
+                                   maxchunks, T, H, I, E, k, sym, s)) != W4A8_OK)
     return rc;
   if (tiles && (rc = mfma_gateup(w_gu, ws_gu, xa, xd, ra.meta, ra.perm, ra.tiles, h, hq, ha, hd,
-                                 gtiles, T, H, I, E, k, s)) != W4A8_OK)
+                                 gtiles, T, H, I, E, k, sym, s)) != W4A8_OK)
     return rc;
   if (ms > 0 && (rc = small_down(w_d, ws_d, hs, ra.meta, ra.perm, ra.chunks, topk_w, shared_w, y,
-                                 maxchunks, T, H, I, E, k, s)) != W4A8_OK)
+                                 maxchunks, T, H, I, E, k, sym, s)) != W4A8_OK)
     return rc;
   if (tiles && (rc = mfma_down(w_d, ws_d, ha, hd, ra.meta, ra.perm, ra.tiles, topk_w, shared_w,
-                               y, gtiles, T, H, I, E, k, s)) != W4A8_OK)
+                               y, gtiles, T, H, I, E, k, sym, s)) != W4A8_OK)
     return rc;
 
   const int64_t n4 = T * (H / 4);
   combine_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s>>>(
       y, ids, out, T, H, (int)k, (int)E, has_shared);
   return check_launch();
+}
+
+}  // namespace
+
+int moe_forward_impl(const float *hidden, DecodeNorm norm, const int32_t *ids,
+                     const float *topk_w, const float *shared_w, const uint8_t *w_gu,
+                     const uint8_t *w_d,
+                     const uint8_t *ws_gu, const uint8_t *ws_d, float *out, int64_t T, int64_t H,
+                     int64_t I, int64_t E, int64_t k, uint8_t *ws, size_t ws_bytes,
+                     hipStream_t s) {
+  const Layout L = make_layout(T, H, I, E, k);
+  int rc;
+  if (norm.gamma) norm.xn = reinterpret_cast<float *>(ws + L.xn);
+
+  // One token: the whole layer in a single launch, the residual RMSNorm
+  // included (see decode.hip).
+  if (T == 1 && decode_supported(H, I, k))
+    return decode_forward(hidden, norm, nullptr, ids, topk_w, shared_w, w_gu, w_d, ws_gu, ws_d, out, H, I,
+                          E, k,
+                          reinterpret_cast<uint32_t *>(ws + L.sync),
+                          reinterpret_cast<uint32_t *>(ws + L.xfer), ws + L.xq,
+                          reinterpret_cast<float *>(ws + L.h), ws + L.hq, s);
+
+  // the pre-norm residual step: inside the quantizing workgroups of the
+  // prep launch when a row fits one of them, else a launch of its own
+  const bool fold_norm = norm.gamma && H / 4 <= ROUTE_T;
+  if (norm.gamma && !fold_norm) {
+    if ((rc = launch_rmsnorm(hidden, norm.resid, norm.gamma, norm.x_out, norm.xn, T, H, norm.eps,
+                             s)) != W4A8_OK)
+      return rc;
+    hidden = norm.xn;
+  }
+  GroupedWs R;
+  R.meta = reinterpret_cast<int32_t *>(ws + L.meta);
+  R.perm = reinterpret_cast<int32_t *>(ws + L.perm);
+  R.count = reinterpret_cast<int32_t *>(ws + L.count);
+  R.rank = reinterpret_cast<int32_t *>(ws + L.rank);
+  R.hist = reinterpret_cast<int32_t *>(ws + L.hist);
+  R.groups = reinterpret_cast<int4 *>(ws + L.groups);
+  R.tiles = reinterpret_cast<int4 *>(ws + L.tiles);
+  R.chunks = reinterpret_cast<int4 *>(ws + L.chunks);
+  R.xq = ws + L.xq;
+  R.h = reinterpret_cast<float *>(ws + L.h);
+  R.hq = ws + L.hq;
+  R.y = reinterpret_cast<float *>(ws + L.y);
+  R.xs = ws + L.xs;
+  R.hs = ws + L.hs;
+  R.xa = reinterpret_cast<uint32_t *>(ws + L.xa);
+  R.xd = reinterpret_cast<float *>(ws + L.xd);
+  R.ha = reinterpret_cast<uint32_t *>(ws + L.ha);
+  R.hd = reinterpret_cast<float *>(ws + L.hd);
+  return grouped_forward(R, hidden, norm, fold_norm, ids, topk_w, shared_w, w_gu, w_d, ws_gu, ws_d,
+                         out, T, H, I, E, k, false, s);
+}
+
+// ------------------------------------------- the grouped fp32-scale format
+// Beside the documented regions and y of the fp32-scale layer's workspace, at
+// `base`: the route's lists, then the activations' second forms (nibble-split
+// for the VALU kernels, aligned for the tiles: one of the two per call).
+namespace {
+GroupedWs sym_grouped_ws(uint8_t *base, int64_t T, int64_t H, int64_t I, int64_t E, int64_t k,
+                         size_t *bytes) {
+  const int64_t P = T * k + T;
+  size_t off = 0;
+  auto take = [&](size_t n) {
+    uint8_t *p = base + off;
+    off += up256(n);
+    return p;
+  };
+  GroupedWs R{};
+  R.meta = reinterpret_cast<int32_t *>(take(256));
+  R.perm = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (P + SMALL_CHUNK)));
+  R.count = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * E));
+  R.rank = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (T * k + 1)));
+  R.hist = reinterpret_cast<int32_t *>(
+      take(sizeof(int32_t) * (size_t)E * ((T * k + SLICE - 1) / SLICE)));
+  R.groups = reinterpret_cast<int4 *>(take(sizeof(int4) * (E + 1)));
+  R.tiles = reinterpret_cast<int4 *>(take(sizeof(int4) * max_tiles(T, E, k)));
+  R.chunks = reinterpret_cast<int4 *>(take(sizeof(int4) * small_max_chunks(T, E, k, 1)));
+  const size_t forms = off;
+  R.xs = take((size_t)T * split_row_bytes(H / QK));
+  R.hs = take((size_t)P * split_row_bytes(I / QK));
+  const size_t split_end = off;
+  off = forms;
+  R.xa = reinterpret_cast<uint32_t *>(take((size_t)T * H));
+  R.xd = reinterpret_cast<float *>(take(sizeof(float) * (size_t)T * (H / QK)));
+  R.ha = reinterpret_cast<uint32_t *>(take((size_t)P * I));
+  R.hd = reinterpret_cast<float *>(take(sizeof(float) * (size_t)P * (I / QK)));
+  *bytes = std::max(off, split_end);
+  return R;
+}
+}  // namespace
+
+size_t sym_grouped_bytes(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
+  size_t n;
+  sym_grouped_ws(nullptr, T, H, I, E, k, &n);
+  return n;
+}
+
+int sym_grouped_forward(const float *hidden, const int32_t *ids, const float *topk_w,
+                        const uint8_t *w_gu, const uint8_t *w_d, const uint8_t *ws_gu,
+                        const uint8_t *ws_d, float *out, uint8_t *xq, float *h, uint8_t *hq,
+                        float *y, uint8_t *base, int64_t T, int64_t H, int64_t I, int64_t E,
+                        int64_t k, hipStream_t s) {
+  size_t n;
+  GroupedWs R = sym_grouped_ws(base, T, H, I, E, k, &n);
+  R.xq = xq;
+  R.h = h;
+  R.hq = hq;
+  R.y = y;
+  return grouped_forward(R, hidden, DecodeNorm{}, false, ids, topk_w, nullptr, w_gu, w_d, ws_gu,
+                         ws_d, out, T, H, I, E, k, true, s);
 }
 
 }  // namespace w4a8

@@ -14,6 +14,8 @@
 //      routed slots in order, then the shared one.
 // (When a token's Q8_F32(h) does not fit LDS, down per (pair, slab) and a
 // separate combine launch instead.)
+// A larger batch runs the grouped kernels of the Q4_0 layer instead (see
+// sym_grouped).
 // The activations of a workgroup sit in LDS in nibble-split form (as in the
 // GEMV of this format), so the block dots are the 4-bit dot products of the
 // Q4_0 path on the stored nibbles.
@@ -23,6 +25,13 @@
 #include "w4a8_host.h"
 
 namespace w4a8 {
+
+size_t sym_grouped_bytes(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k);
+int sym_grouped_forward(const float *hidden, const int32_t *ids, const float *topk_w,
+                        const uint8_t *w_gu, const uint8_t *w_d, const uint8_t *ws_gu,
+                        const uint8_t *ws_d, float *out, uint8_t *xq, float *h, uint8_t *hq,
+                        float *y, uint8_t *base, int64_t T, int64_t H, int64_t I, int64_t E,
+                        int64_t k, hipStream_t s);
 
 namespace {
 
@@ -48,6 +57,18 @@ SymLayout sym_layout(int64_t T, int64_t H, int64_t I, int64_t k) {
   L.y = off;  off += up256(sizeof(float) * (size_t)P * H);
   L.total = off;
   return L;
+}
+
+// A batch whose pairs' weights, read once per pair, come to more than about 80
+// experts of 512 x 2048 takes the grouped kernels of the Q4_0 layer (moe.hip)
+// in this format: sorted by expert, so that an expert's weights are read once
+// for all its tokens.  Top-8 of 256 experts, H = 2048, I = 512, us per layer
+// pair by pair / grouped: 6 tokens 30 / 34, 16 tokens 62 / 46, 32 tokens 113 /
+// 77, 128 tokens 401 / 142, 947 tokens 2708 / 241; of 128 experts, I = 768: 4
+// tokens 35 / 31, 8 tokens 54 / 42.  (The route's slice lists cover E <= 1024.)
+constexpr int64_t SYM_GROUPED_WORK = (int64_t)80 * 512 * 2048;
+inline bool sym_grouped(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
+  return T > 1 && E <= 1024 && T * (k + 1) * I >= (SYM_GROUPED_WORK + H - 1) / H;
 }
 
 int sym_validate(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
@@ -118,16 +139,8 @@ __device__ __forceinline__ void quantize_q8f32_row(const float *x, ActBuf xb, in
     const int blk = t >> 3, j = t & 7;
     const float4 x4 = reinterpret_cast<const float4 *>(x)[t];
     const float v[4] = {x4.x, x4.y, x4.z, x4.w};
-    const float amax =
-        max8(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
-    const float d = amax / 127.0f;
-    const float id = sym_inverse(d);
-    uint32_t packed = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int c = id == 0.0f ? 0 : round_clamp(v[i] * id, 127);
-      packed |= ((uint32_t)c & 0xFFu) << (8 * i);
-    }
+    float d;
+    const uint32_t packed = q8_f32_block8(v, d);
     const int lsum = sum8(low_nibble_sum(packed));
     if (xb.codes) {
       *code_word(xb, blk, j) = split_word(packed, j);
@@ -222,16 +235,8 @@ __global__ __launch_bounds__(SNT) void sym_gateup_kernel(SymArgs a) {
     float v[4];
 #pragma unroll
     for (int i = 0; i < 4; i++) v[i] = silu_f32(vals[4 * j + i]) * vals[32 + 4 * j + i];
-    const float amax =
-        max8(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
-    const float d = amax / 127.0f;
-    const float id = sym_inverse(d);
-    uint32_t packed = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int q = id == 0.0f ? 0 : round_clamp(v[i] * id, 127);
-      packed |= ((uint32_t)q & 0xFFu) << (8 * i);
-    }
+    float d;
+    const uint32_t packed = q8_f32_block8(v, d);
     uint8_t *blk = a.hq + (p * nbh + cb) * Q8FB;
     *reinterpret_cast<uint32_t *>(blk + 4 + 4 * j) = packed;
     if (j == 0) *reinterpret_cast<float *>(blk) = d;
@@ -391,7 +396,7 @@ using namespace w4a8;
 
 extern "C" size_t moe_sym_workspace_size(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
   if (sym_validate(T, H, I, E, k) != W4A8_OK) return 0;
-  return sym_layout(T, H, I, k).total;
+  return sym_layout(T, H, I, k).total + (sym_grouped(T, H, I, E, k) ? sym_grouped_bytes(T, H, I, E, k) : 0);
 }
 
 extern "C" int moe_sym_workspace_layout(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k,
@@ -436,6 +441,11 @@ extern "C" int moe_sym_forward(const float *hidden, const int32_t *topk_ids, con
   a.hq = ws + L.hq;
   a.y = reinterpret_cast<float *>(ws + L.y);
   a.T = T; a.H = H; a.I = I; a.E = E; a.k = k;
+  // (a workspace of the documented regions and y alone stays enough: then the
+  // pairs run one by one)
+  if (sym_grouped(T, H, I, E, k) && ws_bytes >= L.total + sym_grouped_bytes(T, H, I, E, k))
+    return sym_grouped_forward(hidden, topk_ids, topk_w, a.w_gu, a.w_d, a.ws_gu, a.ws_d, out, a.xq,
+                               a.h, a.hq, a.y, ws + L.total, T, H, I, E, k, s);
   const int64_t P = T * k + T;
   const size_t lds_gu = act_buf_bytes((int)(H / QK)) + 64 * sizeof(float);
   // the pairs' workgroups, then one per token row for the documented Q8_F32 copy

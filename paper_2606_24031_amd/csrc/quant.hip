@@ -11,10 +11,10 @@
 
 namespace w4a8 {
 
-// 8 lanes per block (q8_0_lane).
+// 8 lanes per block (q8_lane).
 __global__ __launch_bounds__(256) void q8_0_kernel(const float *__restrict__ x,
                                                    uint8_t *__restrict__ xq, int64_t nblocks) {
-  q8_0_lane(x, xq, nullptr, nullptr, nullptr, nblocks, 1,
+  q8_lane<false>(x, xq, nullptr, nullptr, nullptr, nblocks, 1,
             (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 

@@ -42,6 +42,32 @@ constexpr int WGR_MAX = SNT;       // weight rows per workgroup (LPR = 1)
 
 typedef __attribute__((address_space(4))) const int32_t CInt;
 
+// Eight weight blocks of a row in registers: Q4_0 (144 bytes) or, with SYM, the
+// fp32-scale format (160 bytes).
+template <bool SYM>
+struct GroupOf {
+  using T = W8;
+};
+template <>
+struct GroupOf<true> {
+  using T = W8S;
+};
+template <bool SYM>
+using Group = typename GroupOf<SYM>::T;
+__device__ __forceinline__ void load_group(const uint8_t *p, W8 &w) { load_w8(p, w); }
+__device__ __forceinline__ void load_group(const uint8_t *p, W8S &w) { load_w8s(p, w); }
+__device__ __forceinline__ int group_dot(const W8 &w, int k, uint4 hi, uint4 lo, int corr) {
+  return blockdot_split(w, k, hi, lo, corr);
+}
+__device__ __forceinline__ int group_dot(const W8S &w, int k, uint4 hi, uint4 lo, int corr) {
+  const uint32_t n[4] = {w.D[5 * k + 1], w.D[5 * k + 2], w.D[5 * k + 3], w.D[5 * k + 4]};
+  return blockdot_nib(n, hi, lo, corr);
+}
+__device__ __forceinline__ float group_scale(const W8 &w, int k) { return w8_scale(w, k); }
+__device__ __forceinline__ float group_scale(const W8S &w, int k) {
+  return __builtin_bit_cast(float, w.D[5 * k]);
+}
+
 struct SmallArgs {
   const uint8_t *w, *ws;      // routed experts [E][N][K/32] Q4_0 / shared [N][K/32]
   const uint8_t *act;         // nibble-split activations, rows of K/32 blocks (split_blk)
@@ -84,7 +110,7 @@ __device__ __forceinline__ float row_sum(float v, int lpr) {
 }
 
 // One work item (a workgroup): chunk item / nslab, slab item % nslab.
-template <bool GATEUP>
+template <bool GATEUP, bool SYM>
 __device__ __forceinline__ void small_item(const SmallArgs &a, SmallLds &L, int item) {
   const int c = item / a.nslab, slab = item % a.nslab;
   CInt *cp = (CInt *)a.chunks + 4 * c;
@@ -105,11 +131,12 @@ __device__ __forceinline__ void small_item(const SmallArgs &a, SmallLds &L, int 
   else
     row = (int64_t)slab * wgr + R;
   const bool live = live_g && row < a.N;
-  const int64_t rowbytes = (int64_t)nblk * Q4B;
+  constexpr int BB = SYM ? W4A8_Q4_SYM_BLOCK_BYTES : Q4B;
+  const int64_t rowbytes = (int64_t)nblk * BB;
   const uint8_t *W = (expert < a.E ? a.w + (int64_t)expert * a.N * rowbytes : a.ws) +
-                     (live ? row : 0) * rowbytes + (int64_t)(live ? li : 0) * (8 * Q4B);
-  W8 w;
-  load_w8(W, w);
+                     (live ? row : 0) * rowbytes + (int64_t)(live ? li : 0) * (8 * BB);
+  Group<SYM> w;
+  load_group(W, w);
 
   // the chunk's pairs with one scalar read (the permutation is padded by a
   // chunk), then every activation row straight into LDS (global_load_lds:
@@ -154,8 +181,8 @@ __device__ __forceinline__ void small_item(const SmallArgs &a, SmallLds &L, int 
         for (int kk = 0; kk < 8; kk++) {
           const uint4 hi = ar[3 * kk], lo = ar[3 * kk + 1];
           const uint2 dc = *reinterpret_cast<const uint2 *>(&ar[3 * kk + 2]);
-          const int s = blockdot_split(w, kk, hi, lo, (int)dc.y);
-          acc[m] = fmaf((float)s, w8_scale(w, kk) * __builtin_bit_cast(float, dc.x), acc[m]);
+          const int s = group_dot(w, kk, hi, lo, (int)dc.y);
+          acc[m] = fmaf((float)s, group_scale(w, kk) * __builtin_bit_cast(float, dc.x), acc[m]);
         }
       }
       acc[m] = row_sum(acc[m], lpr);
@@ -184,17 +211,17 @@ __device__ __forceinline__ void small_item(const SmallArgs &a, SmallLds &L, int 
       const int m = t / (bpr * 8), rem = t - m * (bpr * 8), bi = rem >> 3, jj = rem & 7;
       const float *hv = &L.part[m][32 * bi + 4 * jj];
       const float v[4] = {hv[0], hv[1], hv[2], hv[3]};
-      uint32_t d16;
-      const uint32_t packed = q8_0_block8(v, d16);
-      const uint32_t word = split_word(packed, jj);
-      const int lsum = sum8(low_nibble_sum(packed));
       const int p = L.pair[m];
       const int b = slab * bpr + bi;
-      store_q8_0_block8(a.hq + ((int64_t)p * nbh + b) * Q8B, jj, packed, d16);
+      float d;
+      const uint32_t packed =
+          quantize_block8<SYM>(v, a.hq, (int64_t)p * nbh + b, jj, true, d);
+      const uint32_t word = split_word(packed, jj);
+      const int lsum = sum8(low_nibble_sum(packed));
       SplitBlk *hsb = split_blk(a.hs, p, nbh, b);
       hsb->w[jj] = word;
       if (jj == 0) {
-        hsb->d = f16_bits_to_f32(d16);
+        hsb->d = d;
         hsb->corr = -8 * lsum;
       }
     }
@@ -213,11 +240,11 @@ __device__ __forceinline__ void small_item(const SmallArgs &a, SmallLds &L, int 
   }
 }
 
-template <bool GATEUP>
+template <bool GATEUP, bool SYM>
 __global__ __launch_bounds__(SNT) __attribute__((amdgpu_waves_per_eu(4))) void small_kernel(SmallArgs a) {
   __shared__ SmallLds L;
   const int nchunk = ((CInt *)a.meta)[3];   // META_NSMALL
-  if ((int)blockIdx.x < nchunk * a.nslab) small_item<GATEUP>(a, L, blockIdx.x);
+  if ((int)blockIdx.x < nchunk * a.nslab) small_item<GATEUP, SYM>(a, L, blockIdx.x);
 }
 
 // Lanes per weight row: K/256 groups rounded up to a power of two.
@@ -244,7 +271,7 @@ int64_t small_max_chunks(int64_t T, int64_t E, int64_t k, int has_shared) {
 int small_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint8_t *xs,
                  const int32_t *meta, const int32_t *perm, const int4 *chunks, float *h,
                  uint8_t *hq, uint8_t *hs, int64_t maxchunks, int64_t T, int64_t H, int64_t I,
-                 int64_t E, int64_t k, hipStream_t s) {
+                 int64_t E, int64_t k, bool sym, hipStream_t s) {
   SmallArgs a{};
   a.w = w_gu; a.ws = ws_gu; a.act = xs;
   a.meta = meta; a.perm = perm; a.chunks = chunks;
@@ -252,14 +279,18 @@ int small_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint8_t *xs,
   a.T = T; a.k = k; a.E = E; a.N = 2 * I; a.K = H; a.I = I;
   a.lpr = small_lpr(H);
   a.nslab = (int)(I / (256 / a.lpr));          // h columns per workgroup: 256 / lpr
-  small_kernel<true><<<dim3((unsigned)(maxchunks * a.nslab)), dim3(SNT), 0, s>>>(a);
+  const dim3 grid((unsigned)(maxchunks * a.nslab));
+  if (sym)
+    small_kernel<true, true><<<grid, dim3(SNT), 0, s>>>(a);
+  else
+    small_kernel<true, false><<<grid, dim3(SNT), 0, s>>>(a);
   return check_launch();
 }
 
 int small_down(const uint8_t *w_d, const uint8_t *ws_d, const uint8_t *hs, const int32_t *meta,
                const int32_t *perm, const int4 *chunks, const float *topk_w,
                const float *shared_w, float *y, int64_t maxchunks, int64_t T, int64_t H,
-               int64_t I, int64_t E, int64_t k, hipStream_t s) {
+               int64_t I, int64_t E, int64_t k, bool sym, hipStream_t s) {
   SmallArgs a{};
   a.w = w_d; a.ws = ws_d; a.act = hs;
   a.meta = meta; a.perm = perm; a.chunks = chunks;
@@ -268,7 +299,11 @@ int small_down(const uint8_t *w_d, const uint8_t *ws_d, const uint8_t *hs, const
   a.lpr = small_lpr(I);
   const int64_t wgr = SW * (64 / a.lpr);         // down rows per workgroup
   a.nslab = (int)((H + wgr - 1) / wgr);
-  small_kernel<false><<<dim3((unsigned)(maxchunks * a.nslab)), dim3(SNT), 0, s>>>(a);
+  const dim3 grid((unsigned)(maxchunks * a.nslab));
+  if (sym)
+    small_kernel<false, true><<<grid, dim3(SNT), 0, s>>>(a);
+  else
+    small_kernel<false, false><<<grid, dim3(SNT), 0, s>>>(a);
   return check_launch();
 }
 
@@ -289,7 +324,7 @@ int small_dense(const uint8_t *w, const uint8_t *act, const int32_t *meta, const
   a.nslab = (int)((N + wgr - 1) / wgr);
   const int64_t nchunks = (M + SC - 1) / SC;
   if (nchunks * a.nslab >= ((int64_t)1 << 31)) return W4A8_ERANGE;
-  small_kernel<false><<<dim3((unsigned)(nchunks * a.nslab)), dim3(SNT), 0, s>>>(a);
+  small_kernel<false, false><<<dim3((unsigned)(nchunks * a.nslab)), dim3(SNT), 0, s>>>(a);
   return check_launch();
 }
 

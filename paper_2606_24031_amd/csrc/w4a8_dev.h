@@ -304,25 +304,77 @@ __device__ __forceinline__ void store_q8_0_block8(uint8_t *blk, int j, uint32_t 
   if (j == 0) *reinterpret_cast<uint16_t *>(blk) = (uint16_t)d16;
 }
 
+// Reciprocal of a block scale, or 0 when the block's codes are all zero (a
+// zero scale, or one whose reciprocal overflows fp32).
+__device__ __forceinline__ float sym_inverse(float d) {
+  if (d == 0.0f) return 0.0f;
+  const float id = 1.0f / d;                    // correctly rounded division
+  return __builtin_isinf(id) ? 0.0f : id;
+}
+
+__device__ __forceinline__ int round_clamp(float v, int lim) {
+  const int q = (int)roundf(v);                 // half away from zero
+  return q > lim ? lim : (q < -lim ? -lim : q);
+}
+
 // Position of a block's code dword j (elements 4j..4j+3) in the aligned form
 // the matrix-core tiles read: dwords 0 4 1 5 2 6 3 7, so that the elements
 // which share a Q4_0 payload dword are neighbours.
 __host__ __device__ constexpr int aligned_pos(int j) { return 2 * (j & 3) + (j >> 2); }
 
-// Q8_0 of one 32-element block of x by 8 lanes (thread tid: block tid / 8,
-// elements 4 (tid % 8) .. + 3): the 34-byte block, and when the pointers are
-// set its nibble-split form (xs, rows of nbrow blocks, see split_blk) and its
-// 32 codes on a 32-byte boundary (see aligned_pos) with the fp32 scale (xa, xd).  Lanes past
-// nblocks take part in the exchanges and store nothing.  q8_0_lane_vals
-// takes the lane's four values already in registers (elements 4j..4j+3 of
-// block blk; live: the block exists); q8_0_lane loads them from x.
-__device__ __forceinline__ void q8_0_lane_vals(const float v[4], uint8_t *__restrict__ xq,
-                                               uint8_t *__restrict__ xs, uint32_t *__restrict__ xa,
-                                               float *__restrict__ xd, int64_t nbrow, int64_t blk,
-                                               int j, bool live) {
+// Q8_F32 of one 32-value block held by 8 consecutive lanes (as q8_0_block8,
+// with the fp32-scale format's steps: amax, one division by 127, the scale's
+// inverse, round half away from zero, clamp).
+__device__ __forceinline__ uint32_t q8_f32_block8(const float v[4], float &d) {
+  const float amax =
+      max8(fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+  d = amax / 127.0f;
+  const float id = sym_inverse(d);
+  uint32_t packed = 0;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int c = id == 0.0f ? 0 : round_clamp(v[i] * id, 127);
+    packed |= ((uint32_t)c & 0xFFu) << (8 * i);
+  }
+  return packed;
+}
+
+// Activation block blk of a row-major array by 8 lanes, lane j the elements
+// 4j..4j+3: quantized (Q8_0, or with SYM Q8_F32), stored as its 34- or 36-byte
+// block (live lanes), and returned with its fp32 scale.
+template <bool SYM>
+__device__ __forceinline__ uint32_t quantize_block8(const float v[4], uint8_t *q, int64_t blk,
+                                                    int j, bool live, float &d) {
+  if (SYM) {
+    const uint32_t packed = q8_f32_block8(v, d);
+    if (live) {
+      uint8_t *bp = q + blk * W4A8_Q8_F32_BLOCK_BYTES;
+      *reinterpret_cast<uint32_t *>(bp + 4 + 4 * j) = packed;
+      if (j == 0) *reinterpret_cast<float *>(bp) = d;
+    }
+    return packed;
+  }
   uint32_t d16;
   const uint32_t packed = q8_0_block8(v, d16);
-  if (live) store_q8_0_block8(xq + blk * Q8B, j, packed, d16);
+  if (live) store_q8_0_block8(q + blk * Q8B, j, packed, d16);
+  d = f16_bits_to_f32(d16);
+  return packed;
+}
+
+// The quantized block of one 32-element block of x by 8 lanes (thread tid:
+// block tid / 8, elements 4 (tid % 8) .. + 3), and when the pointers are set
+// its nibble-split form (xs, rows of nbrow blocks, see split_blk) and its 32
+// codes on a 32-byte boundary (see aligned_pos) with the fp32 scale (xa, xd).
+// Lanes past nblocks take part in the exchanges and store nothing.
+// q8_lane_vals takes the lane's four values already in registers (elements
+// 4j..4j+3 of block blk; live: the block exists); q8_lane loads them from x.
+template <bool SYM>
+__device__ __forceinline__ void q8_lane_vals(const float v[4], uint8_t *__restrict__ xq,
+                                             uint8_t *__restrict__ xs, uint32_t *__restrict__ xa,
+                                             float *__restrict__ xd, int64_t nbrow, int64_t blk,
+                                             int j, bool live) {
+  float d;
+  const uint32_t packed = quantize_block8<SYM>(v, xq, blk, j, live, d);
   if (xs) {
     const uint32_t word = split_word(packed, j);
     const int lsum = sum8(low_nibble_sum(packed));
@@ -331,21 +383,22 @@ __device__ __forceinline__ void q8_0_lane_vals(const float v[4], uint8_t *__rest
       SplitBlk *sb = split_blk(xs, r, nbrow, blk - r * nbrow);
       sb->w[j] = word;
       if (j == 0) {
-        sb->d = f16_bits_to_f32(d16);
+        sb->d = d;
         sb->corr = -8 * lsum;
       }
     }
   }
   if (xa && live) {
     xa[blk * 8 + aligned_pos(j)] = packed;
-    if (j == 0) xd[blk] = f16_bits_to_f32(d16);
+    if (j == 0) xd[blk] = d;
   }
 }
 
-__device__ __forceinline__ void q8_0_lane(const float *__restrict__ x, uint8_t *__restrict__ xq,
-                                          uint8_t *__restrict__ xs, uint32_t *__restrict__ xa,
-                                          float *__restrict__ xd, int64_t nblocks, int64_t nbrow,
-                                          int64_t tid) {
+template <bool SYM>
+__device__ __forceinline__ void q8_lane(const float *__restrict__ x, uint8_t *__restrict__ xq,
+                                        uint8_t *__restrict__ xs, uint32_t *__restrict__ xa,
+                                        float *__restrict__ xd, int64_t nblocks, int64_t nbrow,
+                                        int64_t tid) {
   const int64_t blk = tid >> 3;
   const int j = (int)(tid & 7);
   float v[4] = {0.f, 0.f, 0.f, 0.f};
@@ -354,7 +407,7 @@ __device__ __forceinline__ void q8_0_lane(const float *__restrict__ x, uint8_t *
     const float4 t = reinterpret_cast<const float4 *>(x + blk * QK)[j];
     v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
   }
-  q8_0_lane_vals(v, xq, xs, xa, xd, nbrow, blk, j, live);
+  q8_lane_vals<SYM>(v, xq, xs, xa, xd, nbrow, blk, j, live);
 }
 
 // LDS staging of activation blocks (see dot8_lds): each block's nibble-split
@@ -390,19 +443,6 @@ __device__ __forceinline__ uint32_t *code_word(ActBuf b, int blk, int j) {
 // the codes of the 8-block group starting at block blk0 (a multiple of 8)
 __device__ __forceinline__ const uint4 *group_codes(ActBuf b, int blk0) {
   return b.codes + (blk0 >> 3) * GROUP_U4;
-}
-
-// Reciprocal of a block scale, or 0 when the block's codes are all zero (a
-// zero scale, or one whose reciprocal overflows fp32).
-__device__ __forceinline__ float sym_inverse(float d) {
-  if (d == 0.0f) return 0.0f;
-  const float id = 1.0f / d;                    // correctly rounded division
-  return __builtin_isinf(id) ? 0.0f : id;
-}
-
-__device__ __forceinline__ int round_clamp(float v, int lim) {
-  const int q = (int)roundf(v);                 // half away from zero
-  return q > lim ? lim : (q < -lim ? -lim : q);
 }
 
 // Eight Q4_SYM blocks of one row (160 bytes) in 40 raw dwords: block k's

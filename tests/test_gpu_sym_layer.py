@@ -97,3 +97,61 @@ def test_sym_layer_exact_integer_layer():
     assert np.array_equal(h[pairs].view(np.uint32), r.h[pairs].view(np.uint32)), "h"
     assert np.array_equal(hq[pairs], r.hq[pairs]), "Q8_F32(h)"
     assert np.array_equal(out.astype(np.float64), r.out), "layer output"
+
+
+# The grouped kernels of this format: VALU chunks of up to 8 rows (9, 40 and
+# 128 tokens), the matrix-core tiles above (129: one slice of the route ranked
+# and finished in one launch; 160 and 400: with groups of a few rows and of
+# more than 64, the routing being skewed), a skipped slot and a repeated
+# expert; I = 256 (two stages of the tiles) to 768.
+@pytest.mark.parametrize("T,H,I,E,k,shared", [(9, 2048, 512, 12, 8, True),
+                                              (40, 1024, 512, 12, 4, True),
+                                              (128, 1024, 512, 5, 2, False),
+                                              (129, 768, 256, 9, 3, True),
+                                              (160, 512, 768, 17, 4, True),
+                                              (400, 256, 256, 40, 3, False)])
+def test_sym_layer_grouped(T, H, I, E, k, shared):
+    print(f"sym grouped T={T} H={H} I={I} E={E} k={k}", flush=True)
+    g = synth.rng(T + H + I + E)
+    w = dict(w_gu=synth.q4_sym_random_blocks(g, E * 2 * I, H),
+             w_d=synth.q4_sym_random_blocks(g, E * H, I),
+             ws_gu=synth.q4_sym_random_blocks(g, 2 * I, H) if shared else None,
+             ws_d=synth.q4_sym_random_blocks(g, H, I) if shared else None)
+    x = synth.normal_f32(g, (T, H))
+    x[1, :32] = 0.0                                     # a zero block
+    ids, wts = synth.routing(g, T, E, k, bias_std=1.0)
+    ids[2, 1] = -1
+    ids[3, 1] = ids[3, 0]
+    gpu_ids = ids.copy()
+    gpu_ids[4, 0] = E                                   # out of range: skipped too
+    ids[4, 0] = -1
+    out, h, hq = run_sym(x, gpu_ids, wts, w, H, I, E, k)
+    moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], w["ws_gu"], w["ws_d"],
+                              H, I, E, k)
+
+
+def test_sym_layer_grouped_workspace_and_in_place():
+    """The documented regions and y alone (what a call of few tokens needs, per
+    token) stay enough for any T: the layer then runs pair by pair, to the
+    same result within the format's tolerance; out may be hidden itself."""
+    T, H, I, E, k = 100, 1024, 512, 8, 2
+    g = synth.rng(65)
+    w_gu, w_d = (dev(synth.q4_sym_random_blocks(g, E * 2 * I, H)),
+                 dev(synth.q4_sym_random_blocks(g, E * H, I)))
+    x = synth.normal_f32(g, (T, H))
+    ids, wts = synth.routing(g, T, E, k)
+    up = lambda n: (n + 255) // 256 * 256
+    P = T * (k + 1)
+    small = up(T * H // 32 * 36) + up(4 * P * I) + up(P * I // 32 * 36) + up(4 * P * H)
+    full = w4.moe_sym_workspace(T, H, I, E, k)
+    assert full.numel() > small
+    outs = []
+    for ws in (full, full[:small].clone()):
+        y = dev(x)
+        w4.moe_sym_forward(y, dev(ids), dev(wts), w_gu, w_d, None, None, H, I, E, k, ws, out=y)
+        outs.append(y.cpu().numpy())
+    # the two sum in another order: a few codes of h may flip by one step
+    assert np.abs(outs[0] - outs[1]).max() <= 1e-2 * np.abs(outs[0]).max()
+    with pytest.raises(w4.W4A8Error):
+        w4.moe_sym_forward(dev(x), dev(ids), dev(wts), w_gu, w_d, None, None, H, I, E, k,
+                           full[:small - 1].clone())
