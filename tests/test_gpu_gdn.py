@@ -56,6 +56,18 @@ def test_gdn_matches_oracle(T, NH, DK, DV, state):
     check(q, k, v, gate, beta, s0, o.cpu().numpy(), s.cpu().numpy(), f"T={T} NH={NH} DK={DK} DV={DV}")
 
 
+# Two to four chunks (both register sets of the scan's loop, its exits), whole
+# and ragged, and value columns that end inside a 16-column workgroup: 8 alone,
+# 24 and 40 past one and two; 1 head and 8 (the per-XCD order)
+@pytest.mark.parametrize("T", [10, 64, 65, 97])
+@pytest.mark.parametrize("NH,DK,DV", [(1, 128, 8), (8, 64, 24), (3, 128, 40)])
+def test_gdn_scan_edges(T, NH, DK, DV):
+    g_ = synth.rng(2000 + T + NH + DV)
+    q, k, v, gate, beta, s0 = synth.gdn_inputs(g_, T, NH, DK, DV, with_state=True)
+    o, s = w4.gdn_scan(dev(q), dev(k), dev(v), dev(gate), dev(beta), dev(s0))
+    check(q, k, v, gate, beta, s0, o.cpu().numpy(), s.cpu().numpy(), f"T={T} NH={NH} DK={DK} DV={DV}")
+
+
 def test_gdn_state_handover_and_in_place_state():
     """Two calls (40, then 30 tokens) with the first call's final state as the
     second's initial state, written in place, against one 70-token run."""
