@@ -38,6 +38,7 @@ namespace {
 constexpr int Q4SB = W4A8_Q4_SYM_BLOCK_BYTES;   // 20
 constexpr int Q8FB = W4A8_Q8_F32_BLOCK_BYTES;   // 36
 constexpr int SNT = 256;
+constexpr int SLOTS_MAX = 65;                   // k <= 64 and the shared pair
 constexpr int64_t SYM_LAYER_K_MAX = 16384;      // H, I: the staged activation row fits LDS
 constexpr size_t SYM_DC_LDS_MAX = 48 * 1024;    // LDS of the fused down + combine workgroup
 
@@ -268,19 +269,6 @@ __global__ __launch_bounds__(SNT) void sym_down_kernel(SymArgs a, int nslab) {
   if (live && li == 0) a.y[p * a.H + n] = wt * s;
 }
 
-// Pair slot q of token t (q == k: the shared pair): its weight in the
-// combine, or false when the slot is skipped or there is no shared expert.
-__device__ __forceinline__ bool slot_live(const SymArgs &a, int64_t t, int q, int has_shared,
-                                          float *wt) {
-  if (q < a.k) {
-    const int e = a.ids[t * a.k + q];
-    *wt = a.topk_w[t * a.k + q];
-    return e >= 0 && e < a.E;
-  }
-  *wt = 1.0f;
-  return has_shared != 0;
-}
-
 // The view of pair slot q's blocks in a buffer that holds nbh blocks per
 // slot (nbh a multiple of 8: whole code groups).
 __device__ __forceinline__ ActBuf slot_view(ActBuf b, int q, int nbh) {
@@ -294,16 +282,24 @@ __device__ __forceinline__ ActBuf slot_view(ActBuf b, int q, int nbh) {
 // Down and combine of one token: workgroup (token t, slab of R output rows).
 // Every pair's Q8_F32(h) of the token is staged in LDS; unit (slot q, row r)
 // takes LPR lanes (groups li, li + LPR, ... as row_dot) and leaves
-// w_q * (its sum) in yv[q][r]; then out[t][n] is the sum of the routed slots
-// in order and then the shared one (the combine kernel's order and fp32
-// steps).
+// w_q * (its sum) in yv[q][r], 0 for a skipped slot; then out[t][n] is the sum
+// of the slots in order, the shared one last (the combine kernel's order and
+// fp32 steps).
+// Latency-bound (1 MB of weights over 150 workgroups): the token's ids and
+// weights are read once into LDS, and the h blocks of all pairs as one run of
+// loads (rows of skipped pairs too: they are not used), SU under way per
+// thread, where a loop over the slots paid a round trip or two for each:
+// one token of top-8 of 256, H = 2048, I = 512: 10.0 -> 5.3 us.
 template <int LPR>
 __global__ __launch_bounds__(SNT) void sym_down_combine_kernel(SymArgs a, float *__restrict__ out,
                                                                int R, int nslab,
                                                                int has_shared) {
   extern __shared__ __align__(16) uint8_t lds[];
+  __shared__ int slot_e[SLOTS_MAX];              // expert of a slot, E: shared, -1: none
+  __shared__ float slot_w[SLOTS_MAX];
+  constexpr int SU = 5;
   const int nbh = (int)(a.I / QK), G = (int)(a.I / 256);
-  const int np = (int)a.k + 1;
+  const int k = (int)a.k, np = k + 1;
   const int64_t t = blockIdx.x / nslab;
   const int slab = (int)(blockIdx.x % nslab);
   const ActBuf hb = act_buf(lds, np * nbh);
@@ -311,56 +307,79 @@ __global__ __launch_bounds__(SNT) void sym_down_combine_kernel(SymArgs a, float 
   const int rpw = SNT / LPR;                  // units per pass
   const int rl = (int)(threadIdx.x / LPR), li = (int)(threadIdx.x % LPR);
   const int64_t rowbytes = (int64_t)nbh * Q4SB;
-  // unit u: slot u / R, row u % R; its weight row (the matrix base when the
-  // unit has none)
-  auto unit = [&](int u, float &wt, bool &live) -> const uint8_t * {
-    const int q = u / R, r = u - q * R;
-    const int64_t n = (int64_t)slab * R + r;
-    wt = 0.0f;
-    live = u < np * R && n < a.H && slot_live(a, t, q, has_shared, &wt);
-    const uint8_t *W = nullptr;
-    if (live) {
-      int64_t tok;
-      W = pair_matrix(a, q < a.k ? t * a.k + q : a.T * a.k + t, false, &tok);
-      live = W != nullptr;
-    }
-    return live ? W + n * rowbytes : a.w_d;
+  // expert of slot q of the token (E: the shared one), -1 for a skipped slot
+  auto expert = [&](int q) -> int {
+    if (q >= k) return has_shared ? (int)a.E : -1;
+    const int e = a.ids[t * k + q];
+    return e >= 0 && e < a.E ? e : -1;
+  };
+  // unit u: slot u / R, row u % R, of expert e: its weight row (the matrix
+  // base when the unit has none)
+  auto unit = [&](int u, int e, bool &live) -> const uint8_t * {
+    const int64_t n = (int64_t)slab * R + u % R;
+    live = u < np * R && n < a.H && e >= 0;
+    if (!live) return a.w_d;
+    return (e < a.E ? a.w_d + (int64_t)e * a.H * rowbytes : a.ws_d) + n * rowbytes;
   };
   // the first pass's weights, issued before the staging
-  float wt0;
   bool live0;
-  const uint8_t *w0 = unit(rl, wt0, live0);
+  const uint8_t *w0 = unit(rl, expert(min(rl / R, k)), live0);
   W8S p0, p1;
   row_pre<LPR>(w0, li, G, p0, p1);
-  for (int q = 0; q < np; q++) {
-    float wt;
-    if (!slot_live(a, t, q, has_shared, &wt)) continue;             // uniform
-    const int64_t p = q < a.k ? t * a.k + q : a.T * a.k + t;
-    stage_q8f32(slot_view(hb, q, nbh), a.hq + p * nbh * Q8FB, nbh);
+  if ((int)threadIdx.x < np) {
+    slot_e[threadIdx.x] = expert((int)threadIdx.x);
+    slot_w[threadIdx.x] = (int)threadIdx.x < k ? a.topk_w[t * k + threadIdx.x] : 1.0f;
+  }
+  // blocks of the routed pairs are one run of memory, the shared pair's follow
+  // in the buffer
+  const uint8_t *const hr = a.hq + t * k * nbh * (int64_t)Q8FB;
+  const uint8_t *const hsh = a.hq + (a.T * k + t) * nbh * (int64_t)Q8FB;
+  const int tot = np * nbh * 8;               // a multiple of 64: whole 8-lane groups
+  for (int i0 = threadIdx.x; i0 < tot; i0 += SU * SNT) {
+    uint32_t packed[SU];
+    float d[SU];
+#pragma unroll
+    for (int u = 0; u < SU; u++) {
+      const int i = min(i0 + u * SNT, tot - 8 + ((int)threadIdx.x & 7));
+      const int blk = i >> 3;
+      const uint8_t *bp = blk < k * nbh ? hr + (int64_t)blk * Q8FB
+                                        : hsh + (int64_t)(blk - k * nbh) * Q8FB;
+      packed[u] = *reinterpret_cast<const uint32_t *>(bp + 4 + 4 * (i & 7));
+      d[u] = *reinterpret_cast<const float *>(bp);
+    }
+#pragma unroll
+    for (int u = 0; u < SU; u++) {
+      const int i = i0 + u * SNT;
+      const uint32_t word = split_word(packed[u], i & 7);
+      const int lsum = sum8(low_nibble_sum(packed[u]));
+      if (i < tot) {
+        *code_word(hb, i >> 3, i & 7) = word;
+        if ((i & 7) == 0) {
+          hb.d[i >> 3] = d[u];
+          hb.corr[i >> 3] = -8 * lsum;
+        }
+      }
+    }
   }
   __syncthreads();
   {
-    const float s = row_dot_pre<LPR>(w0, slot_view(hb, live0 ? rl / R : 0, nbh), li, G, live0,
-                                     p0, p1);
-    if (li == 0 && rl < np * R) yv[rl] = live0 ? wt0 * s : 0.0f;
+    const int q = live0 ? rl / R : 0;
+    const float s = row_dot_pre<LPR>(w0, slot_view(hb, q, nbh), li, G, live0, p0, p1);
+    if (li == 0 && rl < np * R) yv[rl] = live0 ? slot_w[q] * s : 0.0f;
   }
   for (int u0 = rpw; u0 < np * R; u0 += rpw) {
-    const int u = u0 + rl;
-    float wt;
+    const int u = u0 + rl, q = min(u / R, k);
     bool live;
-    const uint8_t *W = unit(u, wt, live);
-    const float s = row_dot<LPR>(W, slot_view(hb, live ? u / R : 0, nbh), li, G, live);
-    if (li == 0 && u < np * R) yv[u] = live ? wt * s : 0.0f;
+    const uint8_t *W = unit(u, slot_e[q], live);
+    const float s = row_dot<LPR>(W, slot_view(hb, q, nbh), li, G, live);
+    if (li == 0 && u < np * R) yv[u] = live ? slot_w[q] * s : 0.0f;
   }
   __syncthreads();
   for (int r = threadIdx.x; r < R; r += SNT) {
     const int64_t n = (int64_t)slab * R + r;
     if (n >= a.H) continue;
     float o = 0.0f;
-    for (int q = 0; q < np; q++) {
-      float wt;
-      if (slot_live(a, t, q, has_shared, &wt)) o += yv[q * R + r];
-    }
+    for (int q = 0; q < np; q++) o += yv[q * R + r];
     out[t * a.H + n] = o;
   }
 }
