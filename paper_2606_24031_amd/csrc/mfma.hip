@@ -384,6 +384,12 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
       Lw[2 * hh + 1][r32] = wscale<SYM>(wl, 1);
     }
     __builtin_amdgcn_wave_barrier();
+    // fp32 scales: a stage's four blocks summed on their own, so that the long
+    // sum's rounding error is no larger than that of the pair-by-pair kernel,
+    // whose rows are summed by four lanes
+    float p0[16], p1[16];
+#pragma unroll
+    for (int e = 0; e < 16; e++) { p0[e] = 0.0f; p1[e] = 0.0f; }
     if constexpr (KIND == T16) {
       const uint32_t *wl = wb + t16 * WDW;
       const float4 d = db[t16];
@@ -398,8 +404,9 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
         const float4 w0 = *reinterpret_cast<const float4 *>(&Lw[j][4 * c16]);
         const float4 w1 = *reinterpret_cast<const float4 *>(&Lw[j][16 + 4 * c16]);
         const float nb = -BIASF * dx[j];
-        scale4<SYM>(acc0, f0[0], f0[1], f0[2], f0[3], dx[j], nb, w0);
-        scale4<SYM>(acc0 + 4, f1[0], f1[1], f1[2], f1[3], dx[j], nb, w1);
+        float *const sum = SYM ? p0 : acc0;
+        scale4<SYM>(sum, f0[0], f0[1], f0[2], f0[3], dx[j], nb, w0);
+        scale4<SYM>(sum + 4, f1[0], f1[1], f1[2], f1[3], dx[j], nb, w1);
       }
     } else {
       const uint32_t *wl = wb + r32 * WDW;
@@ -423,9 +430,13 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
           dw[q] = *reinterpret_cast<const float4 *>(&Lw[j][8 * q + 4 * hh]);
         if (j + 1 < SB) in = block_in<SYM, KIND == T64>(wl, a0, a1, j + 1, hh, sw);
         __builtin_amdgcn_sched_barrier(0);
-        scale16<SYM>(acc0, f0, dx0[j], -BIASF * dx0[j], dw);
-        if (KIND == T64) scale16<SYM>(acc1, f1, dx1[j], -BIASF * dx1[j], dw);
+        scale16<SYM>(SYM ? p0 : acc0, f0, dx0[j], -BIASF * dx0[j], dw);
+        if (KIND == T64) scale16<SYM>(SYM ? p1 : acc1, f1, dx1[j], -BIASF * dx1[j], dw);
       }
+    }
+    if (SYM) {
+#pragma unroll
+      for (int e = 0; e < 16; e++) { acc0[e] += p0[e]; acc1[e] += p1[e]; }
     }
   }
 
@@ -579,7 +590,7 @@ __device__ __forceinline__ void mfma_body(const MArgs &a, MLds &L) {
 }
 
 template <bool GATEUP, bool SYM>
-__global__ __launch_bounds__(MNT) __attribute__((amdgpu_waves_per_eu(3))) void mfma_kernel(MArgs a) {
+__global__ __launch_bounds__(MNT) __attribute__((amdgpu_waves_per_eu(SYM ? 2 : 3))) void mfma_kernel(MArgs a) {
   __shared__ MLds L;
   mfma_body<GATEUP, SYM>(a, L);
 }
