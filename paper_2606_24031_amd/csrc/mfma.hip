@@ -54,8 +54,11 @@
 // 230-244 us; 32 rows over 151936 x 2048 62.8 -> 59.5 us (2.9 TB/s), 947 over
 // 4096 x 2048 34.7 -> 33.6 us.  The down projection lost its resident codes
 // and several slices per workgroup (K <= 512): one slice per workgroup at
-// three per compute unit does as well up to a 947-token prompt, and the long
-// prompt's loss is a sixth of what its gate/up gains.
+// three per compute unit does as well up to a 947-token prompt, and a long
+// prompt loses there about half of what its gate/up gains.  The fp32-scale
+// form (one more operation per output and block, each stage summed on its
+// own: 220 registers, two workgroups per compute unit) takes 125-136 and 80-87
+// us for gate/up and down of 947 tokens.
 #include "w4a8_dev.h"
 #include "w4a8_host.h"
 
