@@ -103,13 +103,15 @@ def test_sym_layer_exact_integer_layer():
 # 128 tokens), the matrix-core tiles above (129: one slice of the route ranked
 # and finished in one launch; 160 and 400: with groups of a few rows and of
 # more than 64, the routing being skewed), a skipped slot and a repeated
-# expert; I = 256 (two stages of the tiles) to 768.
+# expert; I = 256 (two stages of the tiles) to 768; H = 2304, past the VALU
+# kernels' rows, on the tiles at 20 tokens.
 @pytest.mark.parametrize("T,H,I,E,k,shared", [(9, 2048, 512, 12, 8, True),
                                               (40, 1024, 512, 12, 4, True),
                                               (128, 1024, 512, 5, 2, False),
                                               (129, 768, 256, 9, 3, True),
                                               (160, 512, 768, 17, 4, True),
-                                              (400, 256, 256, 40, 3, False)])
+                                              (400, 256, 256, 40, 3, False),
+                                              (20, 2304, 512, 6, 3, True)])
 def test_sym_layer_grouped(T, H, I, E, k, shared):
     print(f"sym grouped T={T} H={H} I={I} E={E} k={k}", flush=True)
     g = synth.rng(T + H + I + E)
