@@ -93,18 +93,30 @@ __device__ __forceinline__ float4 quad(const float *p) {
 // only).  (I + A)^{-1} by blocks of 16: the diagonal blocks by forward
 // substitution, a column per lane of one wave (each column depends only on
 // itself), the block below as -X22 A21 X11, then P T' on the products again.
-// A chain of short steps with three workgroups per compute unit: 22 us for 947
-// tokens of 32 heads (35 with the dot products on the VALU out of LDS, a
-// substitution over all 32 rows and P T' by the same 32 lanes).
+// A chain of short steps, so as many workgroups per compute unit as fit (the
+// matrices take the rows' place in LDS: four): 17 us for 947 tokens of 32 heads
+// (22 with three workgroups; 35 with the dot products on the VALU out of LDS,
+// a substitution over all 32 rows and P T' by the same 32 lanes).
 template <int DK>
 __global__ __launch_bounds__(GNT) void gdn_prep_kernel(GdnArgs a) {
   constexpr int MP = GC + 4;
-  __shared__ __align__(16) float Ks[GC][DK + 4];
-  __shared__ __align__(16) float Qs[GC][DK + 4];
-  __shared__ __align__(16) float Am[GC][MP], Pm[GC][MP];
-  __shared__ __align__(16) float Xt[GC][MP];       // (I + A)^{-1} by column, then T'
-  __shared__ __align__(16) float Mt[16][20];       // A21 X11 by column
+  struct Rows {
+    float K[GC][DK + 4], Q[GC][DK + 4];
+  };
+  struct Mats {
+    float A[GC][MP], P[GC][MP];
+    float Xt[GC][MP];                              // (I + A)^{-1} by column, then T'
+    float Mt[16][20];                              // A21 X11 by column
+  };
+  static_assert(sizeof(Mats) <= sizeof(Rows), "the matrices take the rows' place");
+  __shared__ __align__(16) uint8_t lds[sizeof(Rows)];
   __shared__ float Lc[GC], Bc[GC];
+  float(*const Ks)[DK + 4] = reinterpret_cast<Rows *>(lds)->K;
+  float(*const Qs)[DK + 4] = reinterpret_cast<Rows *>(lds)->Q;
+  float(*const Am)[MP] = reinterpret_cast<Mats *>(lds)->A;
+  float(*const Pm)[MP] = reinterpret_cast<Mats *>(lds)->P;
+  float(*const Xt)[MP] = reinterpret_cast<Mats *>(lds)->Xt;
+  float(*const Mt)[20] = reinterpret_cast<Mats *>(lds)->Mt;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, gq = lane >> 4;
@@ -134,6 +146,7 @@ __global__ __launch_bounds__(GNT) void gdn_prep_kernel(GdnArgs a) {
     const bool isq = wave >= 2;
     const float(*const R)[DK + 4] = isq ? Qs : Ks;
     float(*const D)[MP] = isq ? Pm : Am;
+    v4f c[2];
 #pragma unroll
     for (int jt = 0; jt < 2; jt++) {
       v4f c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
@@ -142,12 +155,16 @@ __global__ __launch_bounds__(GNT) void gdn_prep_kernel(GdnArgs a) {
         for (int kb = 0; kb < DK; kb += 16)
           mm4(quad(&R[16 * it + n][kb + 4 * gq]), quad(&Ks[16 * jt + n][kb + 4 * gq]), c0, c1);
       }
-      c0 += c1;
+      c[jt] = c0 + c1;
+    }
+    __syncthreads();                               // the matrices take the rows' place
+#pragma unroll
+    for (int jt = 0; jt < 2; jt++) {
       const int j = 16 * jt + n;
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         const int i = 16 * it + 4 * gq + e;
-        const float d = j <= i ? expf(Lc[i] - Lc[j]) * c0[e] : 0.0f;
+        const float d = j <= i ? expf(Lc[i] - Lc[j]) * c[jt][e] : 0.0f;
         D[i][j] = isq ? d : (j < i ? Bc[i] * d : 0.0f);
       }
     }
