@@ -96,8 +96,10 @@ struct Layout {
 // to the MFMA tiles, whose 16-row tiles pad a few-row group less than
 // separate VALU launches for those groups cost (947 tokens: 207 us per
 // layer against 214-218 with groups of up to 8 rows on the VALU kernels).
+// A group holds up to T * k rows, not T: a token may name one expert in
+// several slots.
 constexpr int64_t SMALL_T_MAX = 128;
-inline int small_rows(int64_t T) { return T <= SMALL_T_MAX ? (int)SMALL_T_MAX : 0; }
+inline int small_rows(int64_t T, int64_t k) { return T <= SMALL_T_MAX ? (int)(T * k) : 0; }
 
 // Bound on a call's row tiles, at the smaller tile size.
 int64_t max_tiles(int64_t T, int64_t E, int64_t k) {
@@ -843,9 +845,9 @@ int grouped_forward(const GroupedWs &R, const float *hidden, const DecodeNorm &n
                     int64_t I, int64_t E, int64_t k, bool sym, hipStream_t s) {
   const int has_shared = ws_gu != nullptr;
   int rc;
-  const int ms = small_supported(H, I) ? small_rows(T) : 0;
-  // with ms >= T every group (at most T rows) is small: no MFMA tiles
-  const bool tiles = ms < T;
+  const int ms = small_supported(H, I) ? small_rows(T, k) : 0;
+  // either every group is small (ms = T * k) or none (ms = 0)
+  const bool tiles = ms == 0;
   uint8_t *const xs = R.xs, *const hs = R.hs, *const hq = R.hq;
   uint32_t *const xa = R.xa, *const ha = R.ha;
   float *const xd = R.xd, *const hd = R.hd, *const h = R.h, *const y = R.y;

@@ -237,6 +237,20 @@ def test_moe_token_without_pairs_gets_zeros():
         L.check(x, ids_o, wts, k, o, h, hq)
 
 
+@pytest.mark.parametrize("T,k", [(17, 8), (128, 2)])
+def test_moe_one_expert_in_every_slot(T, k):
+    """A batch of up to 128 tokens whose slots all name one expert: a group of
+    more than 128 rows (136 and 256), still on the VALU kernels."""
+    L = Layer(15, 512, 256, 3)
+    g = synth.rng(16 + T)
+    x = synth.normal_f32(g, (T, L.H))
+    ids, wts = synth.routing(g, T, L.E, 1)
+    ids, wts = np.full((T, k), 2, np.int32), np.repeat(wts, k, axis=1)
+    out, h, hq, perm, count, _ = L.run(x, ids, wts, k)
+    _check_route(ids, L.E, True, perm, count)
+    L.check(x, ids, wts, k, out, h, hq)
+
+
 def test_moe_ragged_group_count_and_odd_K():
     """H = I = 768 (three 8-block groups per row, not a power of two)."""
     L = Layer(11, 768, 768, 5)

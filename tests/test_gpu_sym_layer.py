@@ -132,6 +132,22 @@ def test_sym_layer_grouped(T, H, I, E, k, shared):
                               H, I, E, k)
 
 
+def test_sym_layer_grouped_one_expert_in_every_slot():
+    """A group of T * k = 480 rows at 60 tokens, on the VALU chunks."""
+    T, H, I, E, k = 60, 512, 512, 3, 8
+    g = synth.rng(66)
+    w = dict(w_gu=synth.q4_sym_random_blocks(g, E * 2 * I, H),
+             w_d=synth.q4_sym_random_blocks(g, E * H, I),
+             ws_gu=synth.q4_sym_random_blocks(g, 2 * I, H),
+             ws_d=synth.q4_sym_random_blocks(g, H, I))
+    x = synth.normal_f32(g, (T, H))
+    _, wts = synth.routing(g, T, 8, k)
+    ids = np.full((T, k), 1, np.int32)
+    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k)
+    moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], w["ws_gu"], w["ws_d"],
+                              H, I, E, k)
+
+
 def test_sym_layer_grouped_workspace_and_in_place():
     """The documented regions and y alone (what a call of few tokens needs, per
     token) stay enough for any T: the layer then runs pair by pair, to the
