@@ -232,10 +232,11 @@ __device__ __forceinline__ v4f mm16(long a, long b, v4i c) {
 // acc += s * dx * dw of one element; f = 1.5*2^23 + 16 s.  fp16 scales: t =
 // fma(f, dx, nbx) = 16 s dx rounded once (nbx = -1.5*2^23*dx is exact for an
 // 11-bit scale), dw divided by 16.  fp32 scales: that product would round,
-// so s first (exact), then t = s dx.
+// so s alone (exact) times the two scales' product, as the pair-by-pair and
+// VALU kernels form it (s dx first could overflow where dw dx does not).
 template <bool SYM>
 __device__ __forceinline__ float scale1(float acc, float f, float dx, float nbx, float dw) {
-  if (SYM) return fmaf(fmaf(f, 0.0625f, -0.0625f * BIASF) * dx, dw, acc);
+  if (SYM) return fmaf(fmaf(f, 0.0625f, -0.0625f * BIASF), dw * dx, acc);
   return fmaf(fmaf(f, dx, nbx), dw, acc);
 }
 template <bool SYM>

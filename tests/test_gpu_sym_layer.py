@@ -148,6 +148,24 @@ def test_sym_layer_grouped_one_expert_in_every_slot():
                               H, I, E, k)
 
 
+@pytest.mark.parametrize("T", [2, 40, 136])
+def test_sym_layer_scales_near_the_ends_of_fp32(T):
+    """Activations near 6e36 (block scales near 1.4e35) against gate/up scales
+    near 2e-38: the product of the two scales is ordinary, a block dot times the
+    activation scale alone is beyond fp32.  Pair by pair, VALU chunks, tiles."""
+    H, I, E, k = 512, 512, 12, 8
+    g = synth.rng(67 + T)
+    w_gu = synth.q4_sym_random_blocks(g, E * 2 * I, H).reshape(-1, 20).copy()
+    w_gu[:, :4] = (w_gu[:, :4].copy().view(np.float32) * np.float32(3e-36)).view(np.uint8)
+    w = dict(w_gu=w_gu.reshape(E * 2 * I, -1), w_d=synth.q4_sym_random_blocks(g, E * H, I),
+             ws_gu=None, ws_d=None)
+    x = synth.normal_f32(g, (T, H)) * np.float32(6e36)
+    ids, wts = synth.routing(g, T, E, k)
+    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k)
+    assert np.isfinite(out).all()
+    moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], None, None, H, I, E, k)
+
+
 def test_sym_layer_grouped_workspace_and_in_place():
     """The documented regions and y alone (what a call of few tokens needs, per
     token) stay enough for any T: the layer then runs pair by pair, to the
