@@ -289,17 +289,19 @@ __device__ __forceinline__ ActBuf slot_view(ActBuf b, int q, int nbh) {
 // weights are read once into LDS, and the h blocks of all pairs as one run of
 // loads (rows of skipped pairs too: they are not used), SU under way per
 // thread, where a loop over the slots paid a round trip or two for each:
-// one token of top-8 of 256, H = 2048, I = 512: 10.0 -> 5.3 us.
-template <int LPR>
+// one token of top-8 of 256, H = 2048, I = 512: 10.0 -> 5.3 us.  With blocks
+// for at most two rounds of single loads SU is 1 (what is loaded and split past
+// the end is work for nothing): 40 tokens of top-1 of 8, no shared expert: the
+// layer 18.5 -> 15.2 us; 20 of top-2 of 256 24.9 -> 23.4.
+template <int LPR, int SU>
 __global__ __launch_bounds__(SNT) void sym_down_combine_kernel(SymArgs a, float *__restrict__ out,
                                                                int R, int nslab,
                                                                int has_shared) {
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ int slot_e[SLOTS_MAX];              // expert of a slot, E: shared, -1: none
   __shared__ float slot_w[SLOTS_MAX];
-  constexpr int SU = 5;
   const int nbh = (int)(a.I / QK), G = (int)(a.I / 256);
-  const int k = (int)a.k, np = k + 1;
+  const int k = (int)a.k, np = k + has_shared;
   const int64_t t = blockIdx.x / nslab;
   const int slab = (int)(blockIdx.x % nslab);
   const ActBuf hb = act_buf(lds, np * nbh);
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(SNT) void sym_down_combine_kernel(SymArgs a, float 
   const int64_t rowbytes = (int64_t)nbh * Q4SB;
   // expert of slot q of the token (E: the shared one), -1 for a skipped slot
   auto expert = [&](int q) -> int {
-    if (q >= k) return has_shared ? (int)a.E : -1;
+    if (q >= k) return (int)a.E;
     const int e = a.ids[t * k + q];
     return e >= 0 && e < a.E ? e : -1;
   };
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(SNT) void sym_down_combine_kernel(SymArgs a, float 
   };
   // the first pass's weights, issued before the staging
   bool live0;
-  const uint8_t *w0 = unit(rl, expert(min(rl / R, k)), live0);
+  const uint8_t *w0 = unit(rl, expert(min(rl / R, np - 1)), live0);
   W8S p0, p1;
   row_pre<LPR>(w0, li, G, p0, p1);
   if ((int)threadIdx.x < np) {
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(SNT) void sym_down_combine_kernel(SymArgs a, float 
     if (li == 0 && rl < np * R) yv[rl] = live0 ? slot_w[q] * s : 0.0f;
   }
   for (int u0 = rpw; u0 < np * R; u0 += rpw) {
-    const int u = u0 + rl, q = min(u / R, k);
+    const int u = u0 + rl, q = min(u / R, np - 1);
     bool live;
     const uint8_t *W = unit(u, slot_e[q], live);
     const float s = row_dot<LPR>(W, slot_view(hb, q, nbh), li, G, live);
@@ -471,18 +473,19 @@ extern "C" int moe_sym_forward(const float *hidden, const int32_t *topk_ids, con
   sym_gateup_kernel<<<dim3((unsigned)(P * (I / QK) + T)), dim3(SNT), lds_gu, s>>>(a);
   if ((rc = check_launch()) != W4A8_OK) return rc;
   // down and combine in one launch when a token's Q8_F32(h) fits LDS
-  const int np = (int)k + 1;
+  const int hs = ws_gate_up != nullptr;
+  const int np = (int)k + hs;
   const int lpr = I / 256 <= 2 ? 2 : 4;
   const int R = std::max(1, (SNT / lpr) / np);
   const int64_t nslab_dc = (H + R - 1) / R;
   const size_t lds_dc = act_buf_bytes(np * (int)(I / QK)) + sizeof(float) * (size_t)np * R;
   if (lds_dc <= SYM_DC_LDS_MAX && T * nslab_dc < ((int64_t)1 << 31)) {
     const dim3 grid((unsigned)(T * nslab_dc));
-    const int hs = ws_gate_up != nullptr;
-    if (lpr == 2)
-      sym_down_combine_kernel<2><<<grid, dim3(SNT), lds_dc, s>>>(a, out, R, (int)nslab_dc, hs);
-    else
-      sym_down_combine_kernel<4><<<grid, dim3(SNT), lds_dc, s>>>(a, out, R, (int)nslab_dc, hs);
+    const bool few = np * (I / QK) * 8 <= 2 * SNT;
+    auto *const kern =
+        lpr == 2 ? (few ? sym_down_combine_kernel<2, 1> : sym_down_combine_kernel<2, 5>)
+                 : (few ? sym_down_combine_kernel<4, 1> : sym_down_combine_kernel<4, 5>);
+    kern<<<grid, dim3(SNT), lds_dc, s>>>(a, out, R, (int)nslab_dc, hs);
     return check_launch();
   }
   const size_t lds_dn = act_buf_bytes((int)(I / QK));

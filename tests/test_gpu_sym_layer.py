@@ -83,6 +83,27 @@ def test_sym_layer_tokens_no_shared_skipped_slots():
                               H, I, E, k)
 
 
+@pytest.mark.parametrize("T,I,k,shared", [(2, 256, 1, False), (3, 512, 1, False), (2, 512, 1, True),
+                                          (2, 1024, 1, False), (2, 512, 4, False),
+                                          (2, 512, 4, True), (1, 256, 64, True)])
+def test_sym_layer_slot_counts(T, I, k, shared):
+    """Down and combine from one slot (no shared expert) to 65: a token's h
+    blocks of less than one, of one and two whole rounds of single loads per
+    thread, and of more; a repeated expert where k allows."""
+    H, E = 768, 9
+    g = synth.rng(68 + I + k)
+    w = dict(w_gu=synth.q4_sym_random_blocks(g, E * 2 * I, H),
+             w_d=synth.q4_sym_random_blocks(g, E * H, I),
+             ws_gu=synth.q4_sym_random_blocks(g, 2 * I, H) if shared else None,
+             ws_d=synth.q4_sym_random_blocks(g, H, I) if shared else None)
+    x = synth.normal_f32(g, (T, H))
+    ids = g.integers(-1, E, size=(T, k)).astype(np.int32)
+    wts = np.abs(synth.normal_f32(g, (T, k)))
+    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k)
+    moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], w["ws_gu"], w["ws_d"],
+                              H, I, E, k)
+
+
 def test_sym_layer_exact_integer_layer():
     """Every scale 1.0, integer activations and h with block maxima 127: the
     GPU's h, Q8_F32(h) and output equal the oracle's bit for bit (a block dot
