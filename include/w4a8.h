@@ -168,11 +168,12 @@ int q4sym_q8f32_gemv(const void *w, const void *xq, float *y, int64_t N, int64_t
  *   fp32 (may be hidden itself: hidden is read only by the first launch).
  * A few tokens: two launches on the stream (gate/up with the quantization of
  * hidden; down with the combine), or three when a token's Q8_F32(h) of all
- * k + 1 pairs exceeds 48 KiB (down, then the combine on its own).  From
- * T * (k + 1) * H * I >= 80 * 2^20 on (E <= 1024) the grouped kernels of
+ * k + 1 pairs exceeds 48 KiB (down, then the combine on its own).  For a
+ * batch whose tokens share enough experts (E <= 1024) the grouped kernels of
  * moe_w4a8_forward in this format, for which moe_sym_workspace_size asks for
- * more (a workspace of the three regions and P * H floats, each rounded up to
- * 256 bytes, still does: the pairs then run one by one).  The
+ * more from T * (k + 1) * H * I >= 80 * 2^20 on (a workspace of the three
+ * regions and P * H floats, each rounded up to 256 bytes, still does: the
+ * pairs then run one by one).  The
  * workspace (>= moe_sym_workspace_size bytes, no initialisation) holds, at
  * the offsets moe_sym_workspace_layout writes to offsets[0..2]:
  *   W4A8_SYM_WS_XQ  Q8_F32(hidden), [T][H/32] blocks;

@@ -1044,6 +1044,11 @@ GroupedWs sym_grouped_ws(uint8_t *base, int64_t T, int64_t H, int64_t I, int64_t
 }
 }  // namespace
 
+// Whether the grouped fp32-scale layer runs on the VALU chunks (else on the tiles).
+bool sym_grouped_on_valu(int64_t T, int64_t H, int64_t I) {
+  return T <= SMALL_T_MAX && small_supported(H, I);
+}
+
 size_t sym_grouped_bytes(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
   size_t n;
   sym_grouped_ws(nullptr, T, H, I, E, k, &n);

@@ -20,12 +20,14 @@
 // GEMV of this format), so the block dots are the 4-bit dot products of the
 // Q4_0 path on the stored nibbles.
 #include <algorithm>
+#include <cmath>
 
 #include "w4a8_dev.h"
 #include "w4a8_host.h"
 
 namespace w4a8 {
 
+bool sym_grouped_on_valu(int64_t T, int64_t H, int64_t I);
 size_t sym_grouped_bytes(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k);
 int sym_grouped_forward(const float *hidden, const int32_t *ids, const float *topk_w,
                         const uint8_t *w_gu, const uint8_t *w_d, const uint8_t *ws_gu,
@@ -60,16 +62,43 @@ SymLayout sym_layout(int64_t T, int64_t H, int64_t I, int64_t k) {
   return L;
 }
 
-// A batch whose pairs' weights, read once per pair, come to more than about 80
-// experts of 512 x 2048 takes the grouped kernels of the Q4_0 layer (moe.hip)
+// A batch of enough work takes the grouped kernels of the Q4_0 layer (moe.hip)
 // in this format: sorted by expert, so that an expert's weights are read once
-// for all its tokens.  Top-8 of 256 experts, H = 2048, I = 512, us per layer
-// pair by pair / grouped: 6 tokens 30 / 34, 16 tokens 62 / 46, 32 tokens 113 /
-// 77, 128 tokens 401 / 142, 947 tokens 2708 / 241; of 128 experts, I = 768: 4
-// tokens 35 / 31, 8 tokens 54 / 42.  (The route's slice lists cover E <= 1024.)
-constexpr int64_t SYM_GROUPED_WORK = (int64_t)80 * 512 * 2048;
-inline bool sym_grouped(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
-  return T > 1 && E <= 1024 && T * (k + 1) * I >= (SYM_GROUPED_WORK + H - 1) / H;
+// for all its tokens, at three more launches.
+//   * Up to 128 tokens, H and I within the VALU chunks' rows: from 100 experts
+//     of 512 x 2048 read pair by pair on, idle lanes of a row's last round of
+//     groups counted (four lanes per row, two for I <= 512).  us per layer pair
+//     by pair / grouped, H = 2048, I = 512, shared expert: top-8 of 256, 12
+//     tokens 40.5 / 41.7, 16 tokens 52.0 / 46.9, 128 tokens 332 / 139; top-4
+//     of 256, 16 tokens 32.4 / 36.8, 24 tokens 42.9 / 41.5; top-8 of 32, 8 tokens
+//     28.9 / 31.7, 12 tokens 36.4 / 35.0; top-1 of 256, 48 tokens 30.1 / 34.8.
+//   * Else the matrix-core tiles, which pad a group to 16 rows and so only gain
+//     where tokens share experts: besides, pairs at least 1.8 times the distinct
+//     experts they name on average, E (1 - (1 - k/E)^T).  H = 4096, top-8 of 64,
+//     I = 1536: 4 tokens (1.3 times) 84 / 105, 8 tokens (1.7) 148 / 157, 16 tokens
+//     (2.5) 266 / 184; top-2 of 8, I = 14336: 2 tokens (1.1) 78 / 206, 8 tokens
+//     (2.2) 268 / 221; H = 2560, top-8 of 256, I = 512: 32 tokens (1.75) 122 / 132,
+//     48 tokens (2.2) 178 / 156; H = 2048, top-1 of 256, 192 tokens (1.4) 66 / 85.
+// (The route's slice lists cover E <= 1024.)
+constexpr int64_t SYM_GROUPED_WORK = (int64_t)100 * 512 * 2048;
+constexpr int64_t SYM_GROUPED_MIN = (int64_t)80 * 512 * 2048;
+constexpr double SYM_TILES_REUSE = 1.8;
+
+// Whether a call of these sizes may take them: its workspace then has room for
+// both ways (more tokens never need less).
+inline bool sym_may_group(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
+  return T > 1 && E <= 1024 && T * (k + 1) * I >= (SYM_GROUPED_MIN + H - 1) / H;
+}
+bool sym_grouped(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k, bool shared) {
+  if (!sym_may_group(T, H, I, E, k)) return false;
+  const int64_t pairs = T * (k + shared);
+  auto lanes = [](int64_t K, int64_t lpr) { return (K / 256 + lpr - 1) / lpr * lpr * 256; };
+  const int64_t work =
+      pairs * (2 * I * lanes(H, 4) + H * lanes(I, I / 256 <= 2 ? 2 : 4)) / 3;   // < 2^60
+  if (work < SYM_GROUPED_WORK) return false;
+  if (sym_grouped_on_valu(T, H, I)) return true;
+  const double named = k >= E ? (double)E : E * (1.0 - std::pow(1.0 - (double)k / E, (double)T));
+  return pairs >= SYM_TILES_REUSE * (named + shared);
 }
 
 int sym_validate(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
@@ -417,7 +446,8 @@ using namespace w4a8;
 
 extern "C" size_t moe_sym_workspace_size(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k) {
   if (sym_validate(T, H, I, E, k) != W4A8_OK) return 0;
-  return sym_layout(T, H, I, k).total + (sym_grouped(T, H, I, E, k) ? sym_grouped_bytes(T, H, I, E, k) : 0);
+  return sym_layout(T, H, I, k).total +
+         (sym_may_group(T, H, I, E, k) ? sym_grouped_bytes(T, H, I, E, k) : 0);
 }
 
 extern "C" int moe_sym_workspace_layout(int64_t T, int64_t H, int64_t I, int64_t E, int64_t k,
@@ -464,7 +494,8 @@ extern "C" int moe_sym_forward(const float *hidden, const int32_t *topk_ids, con
   a.T = T; a.H = H; a.I = I; a.E = E; a.k = k;
   // (a workspace of the documented regions and y alone stays enough: then the
   // pairs run one by one)
-  if (sym_grouped(T, H, I, E, k) && ws_bytes >= L.total + sym_grouped_bytes(T, H, I, E, k))
+  if (sym_grouped(T, H, I, E, k, ws_gate_up != nullptr) &&
+      ws_bytes >= L.total + sym_grouped_bytes(T, H, I, E, k))
     return sym_grouped_forward(hidden, topk_ids, topk_w, a.w_gu, a.w_d, a.ws_gu, a.ws_d, out, a.xq,
                                a.h, a.hq, a.y, ws + L.total, T, H, I, E, k, s);
   const int64_t P = T * k + T;

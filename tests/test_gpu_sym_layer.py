@@ -23,9 +23,20 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
 
 
-def run_sym(x, ids, wts, w, H, I, E, k):
+def pairs_workspace(T, H, I, k):
+    """Bytes of the documented regions and y: what running pair by pair needs."""
+    up = lambda n: (n + 255) // 256 * 256
+    P = T * (k + 1)
+    return up(T * H // 32 * 36) + up(4 * P * I) + up(P * I // 32 * 36) + up(4 * P * H)
+
+
+def run_sym(x, ids, wts, w, H, I, E, k, grouped=None):
+    """The layer on a workspace filled with a pattern; grouped: whether it is to
+    run on the grouped kernels (which write past the documented regions and
+    y), None: either."""
     T = x.shape[0]
     ws = w4.moe_sym_workspace(T, H, I, E, k)
+    ws.fill_(0xEE)
     sgu = None if w["ws_gu"] is None else dev(w["ws_gu"])
     sd = None if w["ws_d"] is None else dev(w["ws_d"])
     out = w4.moe_sym_forward(dev(x), dev(ids), dev(wts), dev(w["w_gu"]), dev(w["w_d"]), sgu, sd,
@@ -34,6 +45,8 @@ def run_sym(x, ids, wts, w, H, I, E, k):
     lay = w4.moe_sym_workspace_layout(T, H, I, E, k)
     P = T * k + T
     wsn = ws.cpu().numpy()
+    if grouped is not None:
+        assert bool((wsn[pairs_workspace(T, H, I, k):] != 0xEE).any()) == grouped, "path taken"
     h = wsn[lay["h"]:lay["h"] + P * I * 4].view(np.float32).reshape(P, I)
     hq = wsn[lay["hq"]:lay["hq"] + P * (I // 32) * 36].reshape(P, -1)
     xq = wsn[lay["xq"]:lay["xq"] + T * (H // 32) * 36].reshape(T, -1)
@@ -120,14 +133,14 @@ def test_sym_layer_exact_integer_layer():
     assert np.array_equal(out.astype(np.float64), r.out), "layer output"
 
 
-# The grouped kernels of this format: VALU chunks of up to 8 rows (9, 40 and
+# The grouped kernels of this format: VALU chunks of up to 8 rows (13, 44 and
 # 128 tokens), the matrix-core tiles above (129: one slice of the route ranked
 # and finished in one launch; 160 and 400: with groups of a few rows and of
 # more than 64, the routing being skewed), a skipped slot and a repeated
 # expert; I = 256 (two stages of the tiles) to 768; H = 2304, past the VALU
 # kernels' rows, on the tiles at 20 tokens.
-@pytest.mark.parametrize("T,H,I,E,k,shared", [(9, 2048, 512, 12, 8, True),
-                                              (40, 1024, 512, 12, 4, True),
+@pytest.mark.parametrize("T,H,I,E,k,shared", [(13, 2048, 512, 12, 8, True),
+                                              (44, 1024, 512, 12, 4, True),
                                               (128, 1024, 512, 5, 2, False),
                                               (129, 768, 256, 9, 3, True),
                                               (160, 512, 768, 17, 4, True),
@@ -148,7 +161,32 @@ def test_sym_layer_grouped(T, H, I, E, k, shared):
     gpu_ids = ids.copy()
     gpu_ids[4, 0] = E                                   # out of range: skipped too
     ids[4, 0] = -1
-    out, h, hq = run_sym(x, gpu_ids, wts, w, H, I, E, k)
+    out, h, hq = run_sym(x, gpu_ids, wts, w, H, I, E, k, grouped=True)
+    moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], w["ws_gu"], w["ws_d"],
+                              H, I, E, k)
+
+
+# Either side of the dispatch: the VALU chunks by the work of the pairs there
+# are (200 of 512 x 1024, with and without a shared expert), the tiles (H past
+# the chunks' rows, or more than 128 tokens) by how often tokens share an expert.
+@pytest.mark.parametrize("T,H,I,E,k,shared,grouped", [(39, 1024, 512, 12, 4, True, False),
+                                                      (40, 1024, 512, 12, 4, True, True),
+                                                      (49, 1024, 512, 12, 4, False, False),
+                                                      (50, 1024, 512, 12, 4, False, True),
+                                                      (6, 2304, 768, 64, 8, True, False),
+                                                      (12, 2304, 768, 64, 8, True, True),
+                                                      (130, 1024, 768, 128, 1, False, False),
+                                                      (200, 1024, 768, 128, 1, False, True)])
+def test_sym_layer_dispatch(T, H, I, E, k, shared, grouped):
+    print(f"sym dispatch T={T} H={H} I={I} E={E} k={k}", flush=True)
+    g = synth.rng(T + H + I + E + 1)
+    w = dict(w_gu=synth.q4_sym_random_blocks(g, E * 2 * I, H),
+             w_d=synth.q4_sym_random_blocks(g, E * H, I),
+             ws_gu=synth.q4_sym_random_blocks(g, 2 * I, H) if shared else None,
+             ws_d=synth.q4_sym_random_blocks(g, H, I) if shared else None)
+    x = synth.normal_f32(g, (T, H))
+    ids, wts = synth.routing(g, T, E, k)
+    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k, grouped=grouped)
     moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], w["ws_gu"], w["ws_d"],
                               H, I, E, k)
 
@@ -164,7 +202,7 @@ def test_sym_layer_grouped_one_expert_in_every_slot():
     x = synth.normal_f32(g, (T, H))
     _, wts = synth.routing(g, T, 8, k)
     ids = np.full((T, k), 1, np.int32)
-    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k)
+    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k, grouped=True)
     moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], w["ws_gu"], w["ws_d"],
                               H, I, E, k)
 
@@ -182,7 +220,7 @@ def test_sym_layer_scales_near_the_ends_of_fp32(T):
              ws_gu=None, ws_d=None)
     x = synth.normal_f32(g, (T, H)) * np.float32(6e36)
     ids, wts = synth.routing(g, T, E, k)
-    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k)
+    out, h, hq = run_sym(x, ids, wts, w, H, I, E, k, grouped=T > 2)
     assert np.isfinite(out).all()
     moe_check.check_sym_layer(out, h, hq, x, ids, wts, w["w_gu"], w["w_d"], None, None, H, I, E, k)
 
@@ -191,15 +229,13 @@ def test_sym_layer_grouped_workspace_and_in_place():
     """The documented regions and y alone (what a call of few tokens needs, per
     token) stay enough for any T: the layer then runs pair by pair, to the
     same result within the format's tolerance; out may be hidden itself."""
-    T, H, I, E, k = 100, 1024, 512, 8, 2
+    T, H, I, E, k = 110, 1024, 512, 8, 2
     g = synth.rng(65)
     w_gu, w_d = (dev(synth.q4_sym_random_blocks(g, E * 2 * I, H)),
                  dev(synth.q4_sym_random_blocks(g, E * H, I)))
     x = synth.normal_f32(g, (T, H))
     ids, wts = synth.routing(g, T, E, k)
-    up = lambda n: (n + 255) // 256 * 256
-    P = T * (k + 1)
-    small = up(T * H // 32 * 36) + up(4 * P * I) + up(P * I // 32 * 36) + up(4 * P * H)
+    small = pairs_workspace(T, H, I, k)
     full = w4.moe_sym_workspace(T, H, I, E, k)
     assert full.numel() > small
     outs = []
