@@ -285,12 +285,11 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
 
   // the pair of tile row m, or -1 (padding)
   auto row_pair = [&](int m) { return m < rows ? (a.M ? pos + m : a.perm[pos + m]) : -1; };
-  int *const arow = reinterpret_cast<int *>(ring);
-  if (tid < ROWS) {
-    const int p = row_pair(min(tid, rows - 1));   // padding rows read the last row
-    arow[tid] = GATEUP ? (p < a.T * a.k ? p / (int)a.k : p - (int)(a.T * a.k)) : p;
-  }
-  __syncthreads();
+  // its activation row (padding rows read the last row)
+  auto row_act = [&](int m) {
+    const int p = row_pair(min(m, rows - 1)), pr = (int)(a.T * a.k);
+    return GATEUP ? (p < pr ? p / (int)a.k : p - pr) : p;
+  };
 
   // ---- direct loads: this lane's sources
   // weights: the wave's 32 rows as 160 pieces of 16 bytes, piece i of row i / 5
@@ -324,13 +323,12 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
   for (int u = 0; u < CPW; u++) {
     crow[u] = (8 * (CPW * wave + u)) % ROWS;
     const int r = crow[u] + (lane >> 3);
-    csrc[u] = reinterpret_cast<const uint8_t *>(a.act) + (int64_t)arow[r] * nblk * 32 +
+    csrc[u] = reinterpret_cast<const uint8_t *>(a.act) + (int64_t)row_act(r) * nblk * 32 +
               16 * ((lane & 7) ^ ((r >> 1) & 7));
   }
   constexpr int SPW = ROWS / 4;                   // scale rows per wave
   const uint8_t *ssrc = reinterpret_cast<const uint8_t *>(a.actd) +
-                        (int64_t)arow[SPW * wave + (lane & (SPW - 1))] * nblk * 4;
-  __syncthreads();                                // the ring takes arow's place
+                        (int64_t)row_act(SPW * wave + (lane & (SPW - 1))) * nblk * 4;
   auto load_stage = [&](int t) {
     uint8_t *const slot = ring + (t % NS) * SLOT;
     // a stage of Q4_0 is half a 144-byte group: bytes 0..79 or 64..143
@@ -344,6 +342,14 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
       lds_dma16(csrc[u] + t * 128u, slot + SLOT_W + crow[u] * 128);
     if (lane < SPW) lds_dma16(ssrc + t * 16u, slot + SLOT_W + ROWS * 128 + SPW * wave * 16);
   };
+  // the epilogue's pair and combine weight of tile row tid, fetched ahead of the
+  // stages rather than behind the last
+  int ep = -1;
+  float epw = 0.0f;
+  if (tid < ROWS) {
+    ep = row_pair(tid);
+    if (!GATEUP && ep >= 0) epw = pair_weight(a, ep);
+  }
 #pragma unroll
   for (int t = 0; t < NS - 1; t++)
     if (t < S) load_stage(t);
@@ -450,9 +456,8 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
   int *const Lpair = reinterpret_cast<int *>(ring + EPI_BYTES);
   float *const Lpw = reinterpret_cast<float *>(ring + EPI_BYTES + 4 * MT);
   if (tid < ROWS) {
-    const int p = row_pair(tid);
-    Lpair[tid] = p;
-    if (!GATEUP) Lpw[tid] = p >= 0 ? pair_weight(a, p) : 0.0f;
+    Lpair[tid] = ep;
+    if (!GATEUP) Lpw[tid] = epw;
   }
     if (GATEUP) {
       // element e < 8 holds the gate sum and e + 8 the up sum of column
