@@ -59,6 +59,8 @@
 // form (one more operation per output and block, each stage summed on its
 // own: 220 registers, two workgroups per compute unit) takes 125-136 and 80-87
 // us for gate/up and down of 947 tokens.
+#include <algorithm>
+
 #include "w4a8_dev.h"
 #include "w4a8_host.h"
 
@@ -95,7 +97,7 @@ struct MArgs {
   int64_t T, k, E, N, K, I;
   int64_t M;                       // dense product (M > 0): M activation rows in implicit
                                    // tiles of tr rows, one weight matrix (ws), no route
-  int tr;                          // dense product: rows per tile
+  int tr;                          // dense product: rows per tile (16, 32 or 64)
 };
 
 // Weight of pair p in the combine: its routing weight, or for the shared
@@ -343,10 +345,10 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
     if (lane < SPW) lds_dma16(ssrc + t * 16u, slot + SLOT_W + ROWS * 128 + SPW * wave * 16);
   };
   // the epilogue's pair and combine weight of tile row tid, fetched ahead of the
-  // stages rather than behind the last
+  // stages rather than behind the last (a dense product has nothing to fetch)
   int ep = -1;
   float epw = 0.0f;
-  if (tid < ROWS) {
+  if (!a.M && tid < ROWS) {
     ep = row_pair(tid);
     if (!GATEUP && ep >= 0) epw = pair_weight(a, ep);
   }
@@ -456,8 +458,8 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
   int *const Lpair = reinterpret_cast<int *>(ring + EPI_BYTES);
   float *const Lpw = reinterpret_cast<float *>(ring + EPI_BYTES + 4 * MT);
   if (tid < ROWS) {
-    Lpair[tid] = ep;
-    if (!GATEUP) Lpw[tid] = epw;
+    Lpair[tid] = a.M ? row_pair(tid) : ep;
+    if (!GATEUP) Lpw[tid] = a.M ? 1.0f : epw;
   }
     if (GATEUP) {
       // element e < 8 holds the gate sum and e + 8 the up sum of column
@@ -652,7 +654,15 @@ int mfma_dense(const uint8_t *w, const uint32_t *act, const float *actd, float *
   a.w = nullptr; a.ws = w; a.act = act; a.actd = actd; a.y = y;
   a.T = 0; a.k = 0; a.E = 0; a.N = N; a.K = K; a.I = K; a.M = M;
   const int64_t nsl = (N + WROWS - 1) / WROWS;
+  // Smaller tiles while each still has a compute unit to itself: a workgroup
+  // alone on its unit overlaps nothing, so its time goes by its tile's rows.  us
+  // at 64 / 32 / 16 rows: 129 x 2048 x 2048 (48, 80, 144 workgroups) 22.4 / 18.5 /
+  // 14.9, 400 x 2048 x 2048 (112, 208, 400) 23.3 / 19.8 / 19.3, 700 x 2048 x 2048
+  // (176, 352, 704) 24.4 / 25.0 / 25.4, 64 x 2048 x 4096 (16, 32, 64) 38.2 / 31.5 /
+  // 24.3, 256 x 8192 x 4096 (256, 512, 1024) 40.8 / 42.0 / 56.2.
+  const int64_t cus = std::max(1, device_cus());
   a.tr = MT;
+  for (int tr = MT / 2; tr >= 16 && nsl * ((M + tr - 1) / tr) <= cus; tr /= 2) a.tr = tr;
   const int64_t ntiles = (M + a.tr - 1) / a.tr;
   const int64_t grid = 8 * ((nsl * ntiles + 7) / 8);    // an XCD takes at most ceil(items/8)
   if (grid >= ((int64_t)1 << 31)) return W4A8_ERANGE;

@@ -66,6 +66,22 @@ def test_gemm_tile_ring_edges(M, N, K):
     _rows_check(y, w, xq, N, K, range(M))
 
 
+# Dense tiles of 32 and 64 rows (taken where smaller ones would outnumber the
+# compute units; the cases above have few enough columns for 16): last tiles of 1,
+# 17, 32, 33 and 64 rows, one tile of 33 and of 64, an unaligned row length.
+@pytest.mark.parametrize("M,N,K", [(129, 4000, 256), (145, 4000, 512), (160, 4001, 256),
+                                   (161, 4000, 2304), (129, 16500, 256), (145, 16500, 512),
+                                   (161, 16501, 256), (192, 16500, 512), (33, 16500, 2304),
+                                   (64, 16500, 2304)])
+def test_gemm_larger_tiles(M, N, K):
+    print(f"gemm larger tiles M={M} N={N} K={K}", flush=True)
+    g = synth.rng(5 * M + N + K)
+    w = synth.q4_0_random_blocks(g, N, K).reshape(N, -1)
+    xq = oracle.q8_0_quantize(synth.normal_f32(g, (M, K))).reshape(M, -1)
+    y = w4.q4q8_gemm(dev(w), dev(xq), M, N, K).cpu().numpy()
+    _rows_check(y, w, xq, N, K, range(M))
+
+
 def test_gemm_prefill_rows_sampled():
     """947 rows (14 full tiles and a 51-row tile) at the dense layer shape
     N = 2048, K = 2048: 40 sampled rows and the first and last."""
