@@ -31,7 +31,7 @@ std::atomic<int> g_arch[kMaxDevices];
 std::atomic<int> g_cus[kMaxDevices];   // compute units, set with g_arch
 }  // namespace
 
-int check_device() {
+int check_device(int *cus) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return W4A8_EHIP;
   if (dev < 0 || dev >= kMaxDevices) return W4A8_EDEVICE;
@@ -43,6 +43,7 @@ int check_device() {
     g_cus[dev].store(prop.multiProcessorCount, std::memory_order_relaxed);
     g_arch[dev].store(state, std::memory_order_relaxed);
   }
+  if (cus) *cus = g_cus[dev].load(std::memory_order_relaxed);
   return state == 1 ? W4A8_OK : W4A8_EDEVICE;
 }
 

@@ -15,7 +15,7 @@
 namespace w4a8 {
 
 int mfma_dense(const uint8_t *w, const uint32_t *act, const float *actd, float *y, int64_t M,
-               int64_t N, int64_t K, hipStream_t s);
+               int64_t N, int64_t K, int cus, hipStream_t s);
 bool small_supported(int64_t H, int64_t I);
 int small_dense(const uint8_t *w, const uint8_t *act, const int32_t *meta, const int32_t *perm,
                 const int4 *chunks, float *y, int64_t M, int64_t N, int64_t K, hipStream_t s);
@@ -155,7 +155,8 @@ extern "C" int q4q8_gemm(const void *w, const void *xq, float *y, int64_t M, int
   if (!workspace) return W4A8_ENULL;
   if (!aligned16(workspace)) return W4A8_EALIGN;
   if (ws_bytes < q4q8_gemm_workspace_size(M, K)) return W4A8_EWORKSPACE;
-  if ((rc = check_device()) != W4A8_OK) return rc;
+  int cus;
+  if ((rc = check_device(&cus)) != W4A8_OK) return rc;
   hipStream_t s = as_stream(stream);
   uint8_t *ws = reinterpret_cast<uint8_t *>(workspace);
   if (dense_small(M, N, K)) {
@@ -177,5 +178,5 @@ extern "C" int q4q8_gemm(const void *w, const void *xq, float *y, int64_t M, int
   align_q8_0_kernel<<<dim3((unsigned)((nblocks * 8 + 255) / 256)), dim3(256), 0, s>>>(
       reinterpret_cast<const uint8_t *>(xq), act, actd, nblocks);
   if ((rc = check_launch()) != W4A8_OK) return rc;
-  return mfma_dense(reinterpret_cast<const uint8_t *>(w), act, actd, y, M, N, K, s);
+  return mfma_dense(reinterpret_cast<const uint8_t *>(w), act, actd, y, M, N, K, cus, s);
 }

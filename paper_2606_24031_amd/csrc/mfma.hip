@@ -97,7 +97,7 @@ struct MArgs {
   int64_t T, k, E, N, K, I;
   int64_t M;                       // dense product (M > 0): M activation rows in implicit
                                    // tiles of tr rows, one weight matrix (ws), no route
-  int tr;                          // dense product: rows per tile (16, 32 or 64)
+  int tr, run;                     // dense product: rows per tile (16, 32 or 64), slices per run
 };
 
 // Weight of pair p in the combine: its routing weight, or for the shared
@@ -566,17 +566,21 @@ __device__ __forceinline__ void mfma_body(const MArgs &a, MLds &L) {
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
   int expert, pos, rows, slice;
   if (a.M) {
-    // Dense products: the items in slice-major order (all 64-row tiles of
-    // the activations for one slice of weight rows in a row), XCD x taking
-    // the x-th of 8 even contiguous runs: the tiles of one slice share its
-    // weights in that XCD's L2, and every XCD streams its own part of the
-    // weights, so a handful of tiles still spreads over all 8.
+    // Dense products: runs of `run` slices of weight rows, within a run the
+    // tiles in order, all the run's slices of a tile in a row, XCD x taking the
+    // x-th of 8 even contiguous parts: a run's weights and a tile's codes are
+    // shared in that XCD's L2, every XCD streams its own part of the weights
+    // (so a handful of tiles still spreads over all 8), and an output row is
+    // written in pieces of run * 512 bytes (one slice at a time, 512, reached
+    // less of the memory's rate; see mfma_dense).
     const int ntl = (int)((a.M + a.tr - 1) / a.tr);
     const int tot = nsl * ntl;
     const int i0 = x * tot / 8, nx = (x + 1) * tot / 8 - i0;
     if (q >= nx) return;
-    slice = (i0 + q) / ntl;
-    const int tile = (i0 + q) - slice * ntl;
+    const int r = (i0 + q) / (ntl * a.run), in = (i0 + q) - r * (ntl * a.run);
+    const int w = min(a.run, nsl - r * a.run);
+    const int tile = in / w;
+    slice = r * a.run + in - tile * w;
     expert = 0;                  // E = 0: the weights are ws
     pos = tile * a.tr;
     rows = (int)min((int64_t)a.tr, a.M - pos);
@@ -649,7 +653,7 @@ int mfma_down(const uint8_t *w_d, const uint8_t *ws_d, const uint32_t *ha, const
 // Dense product y[m][n] = sum_b d_w[n,b] d_x[m,b] s[m,n,b] of M activation
 // rows (aligned codes and fp32 scales) with one weight matrix [N][K/32].
 int mfma_dense(const uint8_t *w, const uint32_t *act, const float *actd, float *y, int64_t M,
-               int64_t N, int64_t K, hipStream_t s) {
+               int64_t N, int64_t K, int cus, hipStream_t s) {
   MArgs a{};
   a.w = nullptr; a.ws = w; a.act = act; a.actd = actd; a.y = y;
   a.T = 0; a.k = 0; a.E = 0; a.N = N; a.K = K; a.I = K; a.M = M;
@@ -660,9 +664,14 @@ int mfma_dense(const uint8_t *w, const uint32_t *act, const float *actd, float *
   // 14.9, 400 x 2048 x 2048 (112, 208, 400) 23.3 / 19.8 / 19.3, 700 x 2048 x 2048
   // (176, 352, 704) 24.4 / 25.0 / 25.4, 64 x 2048 x 4096 (16, 32, 64) 38.2 / 31.5 /
   // 24.3, 256 x 8192 x 4096 (256, 512, 1024) 40.8 / 42.0 / 56.2.
-  const int64_t cus = std::max(1, device_cus());
   a.tr = MT;
   for (int tr = MT / 2; tr >= 16 && nsl * ((M + tr - 1) / tr) <= cus; tr /= 2) a.tr = tr;
+  // Runs of 16 slices while their weights fill no more than 2.5 of an L2's 4 MB.
+  // us with runs of 1 / 4 / 16: 4096 x 151936 x 256 820 / 743 / 734, 16384 x 2048 x
+  // 512 75.3 / 72.9 / 67.6, 4096 x 2048 x 1024 38.2 / 37.9 / 34.5, 947 x 2048 x 2048
+  // 25.6 / 25.4 / 24.2; at K = 4096 (8 slices) 4096 x 8192 386 / 389 / 376.
+  const int64_t slice_bytes = WROWS * (K / 32) * Q4B;
+  a.run = (int)std::max<int64_t>(1, std::min<int64_t>(16, ((int64_t)5 << 19) / slice_bytes));
   const int64_t ntiles = (M + a.tr - 1) / a.tr;
   const int64_t grid = 8 * ((nsl * ntiles + 7) / 8);    // an XCD takes at most ceil(items/8)
   if (grid >= ((int64_t)1 << 31)) return W4A8_ERANGE;

@@ -9,8 +9,8 @@
 namespace w4a8 {
 
 // W4A8_OK if the current device is gfx950, else W4A8_EDEVICE / W4A8_EHIP.
-// Cached per device after the first query.
-int check_device();
+// Cached per device after the first query.  cus (not null): its compute units.
+int check_device(int *cus = nullptr);
 
 // W4A8_EHIP if a launch on this thread failed since the last check.
 int check_launch();
