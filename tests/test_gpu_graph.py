@@ -1,7 +1,8 @@
 """The grouped layer with groups of every tile kind (a few rows on 16-row
 tiles, larger ones on 32- and 64-row tiles): parity with the oracle,
 run-to-run bit equality, and the same bits from a captured HIP graph
-replayed several times with other eager calls in between (GPU)."""
+replayed several times with other eager calls in between; the fp32-scale
+layer's grouped kernels likewise (GPU)."""
 import numpy as np
 import pytest
 
@@ -57,4 +58,37 @@ def test_grouped_layer_parity_determinism_and_graph_replays():
         torch.cuda.synchronize()
         assert np.array_equal(out_g.cpu().numpy(), o0), f"replay {rep}"
         w4.moe_forward(x2, idd, wd, d_gu, d_d, d_sgu, d_sd, H, I, E, K, ws2)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("T", [48, 136])
+def test_sym_grouped_layer_determinism_and_graph_replays(T):
+    """The fp32-scale layer of a batch on the VALU chunks (48 tokens) and on the
+    tiles (136): the same bits from a second eager call and from a graph
+    replayed between other calls."""
+    H, I, E, K = 1024, 512, 32, 4
+    g = synth.rng(4243 + T)
+    d_gu, d_d = (dev(synth.q4_sym_random_blocks(g, E * 2 * I, H)),
+                 dev(synth.q4_sym_random_blocks(g, E * H, I)))
+    d_sgu, d_sd = dev(synth.q4_sym_random_blocks(g, 2 * I, H)), dev(synth.q4_sym_random_blocks(g, H, I))
+    ids, wts = synth.routing(g, T, E, K, bias_std=1.0)
+    xd, idd, wd = dev(synth.normal_f32(g, (T, H))), dev(ids), dev(wts)
+    x2 = dev(synth.normal_f32(g, (T, H)))
+    ws, ws2 = w4.moe_sym_workspace(T, H, I, E, K), w4.moe_sym_workspace(T, H, I, E, K)
+
+    def call(x, ws, out=None):
+        return w4.moe_sym_forward(x, idd, wd, d_gu, d_d, d_sgu, d_sd, H, I, E, K, ws, out=out)
+
+    o0 = call(xd, ws).cpu().numpy()
+    assert np.array_equal(call(xd, ws).cpu().numpy(), o0)
+    out_g = torch.empty((T, H), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(xd, ws, out_g)
+    for rep in range(3):
+        out_g.fill_(0.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out_g.cpu().numpy(), o0), f"replay {rep}"
+        call(x2, ws2)
         torch.cuda.synchronize()

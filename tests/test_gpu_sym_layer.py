@@ -122,15 +122,33 @@ def test_sym_layer_exact_integer_layer():
     GPU's h, Q8_F32(h) and output equal the oracle's bit for bit (a block dot
     off by one anywhere changes them)."""
     H, I, E, k = 2048, 512, 8, 4
-    L = ExactLayer(64, H, I, E, k, [(3, [1, 5, -1, 7])], shared=True, lo=1)
+    check_exact(ExactLayer(64, H, I, E, k, [(3, [1, 5, -1, 7])], shared=True, lo=1), H, I, False)
+
+
+def check_exact(L, H, I, grouped):
     w_gu, w_d, ws_gu, ws_d = L.sym()
     w = dict(w_gu=w_gu, w_d=w_d, ws_gu=ws_gu, ws_d=ws_d)
-    out, h, hq = run_sym(L.x, L.ids, L.wts, w, H, I, E, k)
-    r = oracle.moe_sym(L.x, L.ids, L.wts, w_gu, w_d, ws_gu, ws_d, H, I, E, k)
-    pairs = moe_check.valid_pairs(L.ids, E, True)
+    out, h, hq = run_sym(L.x, L.ids, L.wts, w, H, I, L.E, L.k, grouped=grouped)
+    r = oracle.moe_sym(L.x, L.ids, L.wts, w_gu, w_d, ws_gu, ws_d, H, I, L.E, L.k)
+    pairs = moe_check.valid_pairs(L.ids, L.E, ws_gu is not None)
     assert np.array_equal(h[pairs].view(np.uint32), r.h[pairs].view(np.uint32)), "h"
     assert np.array_equal(hq[pairs], r.hq[pairs]), "Q8_F32(h)"
     assert np.array_equal(out.astype(np.float64), r.out), "layer output"
+
+
+@pytest.mark.parametrize("E,k,clusters,shared", [
+    # VALU chunks: three clusters of one chunk; chunks of 8, 8 and 4 rows
+    (24, 8, [(8, range(0, 8)), (8, range(8, 16)), (8, range(16, 24))], False),
+    (8, 8, [(20, range(8))], True),
+    # tiles, cut at 64 rows: groups of 40, 70 (a full tile and one of 6 rows), 5,
+    # 16 and 17; cut at 32 rows: 150 rows and the shared group
+    (128, 8, [(40, range(0, 8)), (70, range(8, 16)), (5, range(16, 24)), (16, range(24, 32)),
+              (17, range(32, 40))], False),
+    (8, 8, [(150, range(8))], True)])
+def test_sym_layer_exact_integer_layer_grouped(E, k, clusters, shared):
+    H, I = 2048, 512
+    L = ExactLayer(69 + E, H, I, E, k, [(n, list(e)) for n, e in clusters], shared=shared, lo=1)
+    check_exact(L, H, I, True)
 
 
 # The grouped kernels of this format: VALU chunks of up to 8 rows (13, 44 and
