@@ -284,7 +284,7 @@ __global__ __launch_bounds__(SNT) void gdn_scan_kernel(GdnArgs a) {
   const int cb = sl * DVS;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, gq = lane >> 4;
-  const bool col = cb + n < a.DV;        // a last slice past DV computes zero columns
+  const bool col = cb + n < a.DV;        // columns past DV repeat the last one, unstored
   // rows 16 wave + 4 gq + e of column n
   v4f S = {0.f, 0.f, 0.f, 0.f};
   if (wave < NT && a.s0 && col) {

@@ -461,17 +461,17 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
     Lpair[tid] = a.M ? row_pair(tid) : ep;
     if (!GATEUP) Lpw[tid] = a.M ? 1.0f : epw;
   }
-    if (GATEUP) {
-      // element e < 8 holds the gate sum and e + 8 the up sum of column
-      // 16*wave + 8*(e/4) + 4*hh + e%4 for this lane's token (16-row tiles:
-      // e < 4 gate and e + 4 up of column 16*wave + 4*(lane/16) + e of
-      // token lane%16)
-      if constexpr (KIND == T16) {
-        const float *acc = acc0;
-        *reinterpret_cast<float4 *>(&hv[lane & 15][16 * wave + 4 * (lane >> 4)]) =
-            make_float4(silu_f32(acc[0]) * acc[4], silu_f32(acc[1]) * acc[5],
-                        silu_f32(acc[2]) * acc[6], silu_f32(acc[3]) * acc[7]);
-      } else {
+  if (GATEUP) {
+    // element e < 8 holds the gate sum and e + 8 the up sum of column
+    // 16*wave + 8*(e/4) + 4*hh + e%4 for this lane's token (16-row tiles:
+    // e < 4 gate and e + 4 up of column 16*wave + 4*(lane/16) + e of
+    // token lane%16)
+    if constexpr (KIND == T16) {
+      const float *acc = acc0;
+      *reinterpret_cast<float4 *>(&hv[lane & 15][16 * wave + 4 * (lane >> 4)]) =
+          make_float4(silu_f32(acc[0]) * acc[4], silu_f32(acc[1]) * acc[5],
+                      silu_f32(acc[2]) * acc[6], silu_f32(acc[3]) * acc[7]);
+    } else {
 #pragma unroll
       for (int half = 0; half < (KIND == T64 ? 2 : 1); half++) {
         const float *acc = half ? acc1 : acc0;
@@ -484,74 +484,74 @@ __device__ __forceinline__ void mfma_tile(const MArgs &a, MLds &L, int expert, i
                           silu_f32(acc[4 * q + 2]) * acc[4 * q + 10],
                           silu_f32(acc[4 * q + 3]) * acc[4 * q + 11]);
       }
-      }
-      __syncthreads();
-      // Q8_0 of each row's two 32-wide blocks: 8 lanes per block
-      const int nbh = (int)(a.I / 32);
+    }
+    __syncthreads();
+    // Q8_0 of each row's two 32-wide blocks: 8 lanes per block
+    const int nbh = (int)(a.I / 32);
 #pragma unroll
-      for (int pass = 0; pass < ROWS * 16 / MNT; pass++) {
-        const int idx = pass * MNT + tid;
-        const int rb = idx >> 3, jq = idx & 7, m = rb >> 1, cb = rb & 1;
-        const int p = Lpair[m];
-        if (p >= 0) {                             // whole 8-lane groups agree
-          const float4 hv4 = *reinterpret_cast<const float4 *>(&hv[m][32 * cb + 4 * jq]);
-          const float v[4] = {hv4.x, hv4.y, hv4.z, hv4.w};
-          const int bi = 2 * slice + cb;
-          const int64_t blk = (int64_t)p * nbh + bi;
-          float d;
-          const uint32_t packed = quantize_block8<SYM>(v, a.hq, blk, jq, true, d);
-          a.ha[blk * 8 + aligned_pos(jq)] = packed;
-          if (jq == 0) a.hd[blk] = d;
-          *reinterpret_cast<float4 *>(a.h + (int64_t)p * a.I + 32 * bi + 4 * jq) = hv4;
-        }
-      }
-    } else {
-      __syncthreads();
-      // w * y of the tile through LDS, so that half a wave stores a whole row
-      // of 512 bytes instead of 32-byte pieces of 32 rows: element 4q + i is
-      // column 32*wave + 8q + 4hh + i of the slice (16-row tiles: of token
-      // lane%16, column 32*wave + 16q + 4*(lane/16) + i)
-      constexpr int YVS = WROWS + 4;
-      float *const yt = reinterpret_cast<float *>(ring);
-      static_assert(MT * YVS * 4 <= EPI_BYTES, "the output tile fits the epilogue");
-      if constexpr (KIND == T16) {
-        const float pw = Lpw[t16];
-#pragma unroll
-        for (int q = 0; q < 2; q++)
-          *reinterpret_cast<float4 *>(yt + t16 * YVS + 32 * wave + 16 * q + 4 * c16) =
-              make_float4(pw * acc0[4 * q], pw * acc0[4 * q + 1], pw * acc0[4 * q + 2],
-                          pw * acc0[4 * q + 3]);
-      } else {
-#pragma unroll
-        for (int half = 0; half < (KIND == T64 ? 2 : 1); half++) {
-          const float *acc = half ? acc1 : acc0;
-          const float pw = Lpw[32 * half + r32];
-#pragma unroll
-          for (int q = 0; q < 4; q++)
-            *reinterpret_cast<float4 *>(yt + (32 * half + r32) * YVS + 32 * wave + 8 * q + 4 * hh) =
-                make_float4(pw * acc[4 * q], pw * acc[4 * q + 1], pw * acc[4 * q + 2],
-                            pw * acc[4 * q + 3]);
-        }
-      }
-      __syncthreads();
-      const bool vec = (a.N & 3) == 0;
-      const int64_t n = (int64_t)slice * WROWS + 4 * r32;
-#pragma unroll
-      for (int u = 0; u < ROWS / 8; u++) {
-        const int m = 8 * u + 2 * wave + hh, p = Lpair[m];
-        if (p < 0 || n >= a.N) continue;
-        const float4 v = *reinterpret_cast<const float4 *>(yt + m * YVS + 4 * r32);
-        float *yp = a.y + (int64_t)p * a.N + n;
-        if (vec) {
-          *reinterpret_cast<float4 *>(yp) = v;
-        } else {
-          yp[0] = v.x;
-          if (n + 1 < a.N) yp[1] = v.y;
-          if (n + 2 < a.N) yp[2] = v.z;
-          if (n + 3 < a.N) yp[3] = v.w;
-        }
+    for (int pass = 0; pass < ROWS * 16 / MNT; pass++) {
+      const int idx = pass * MNT + tid;
+      const int rb = idx >> 3, jq = idx & 7, m = rb >> 1, cb = rb & 1;
+      const int p = Lpair[m];
+      if (p >= 0) {                             // whole 8-lane groups agree
+        const float4 hv4 = *reinterpret_cast<const float4 *>(&hv[m][32 * cb + 4 * jq]);
+        const float v[4] = {hv4.x, hv4.y, hv4.z, hv4.w};
+        const int bi = 2 * slice + cb;
+        const int64_t blk = (int64_t)p * nbh + bi;
+        float d;
+        const uint32_t packed = quantize_block8<SYM>(v, a.hq, blk, jq, true, d);
+        a.ha[blk * 8 + aligned_pos(jq)] = packed;
+        if (jq == 0) a.hd[blk] = d;
+        *reinterpret_cast<float4 *>(a.h + (int64_t)p * a.I + 32 * bi + 4 * jq) = hv4;
       }
     }
+  } else {
+    __syncthreads();
+    // w * y of the tile through LDS, so that half a wave stores a whole row
+    // of 512 bytes instead of 32-byte pieces of 32 rows: element 4q + i is
+    // column 32*wave + 8q + 4hh + i of the slice (16-row tiles: of token
+    // lane%16, column 32*wave + 16q + 4*(lane/16) + i)
+    constexpr int YVS = WROWS + 4;
+    float *const yt = reinterpret_cast<float *>(ring);
+    static_assert(MT * YVS * 4 <= EPI_BYTES, "the output tile fits the epilogue");
+    if constexpr (KIND == T16) {
+      const float pw = Lpw[t16];
+#pragma unroll
+      for (int q = 0; q < 2; q++)
+        *reinterpret_cast<float4 *>(yt + t16 * YVS + 32 * wave + 16 * q + 4 * c16) =
+            make_float4(pw * acc0[4 * q], pw * acc0[4 * q + 1], pw * acc0[4 * q + 2],
+                        pw * acc0[4 * q + 3]);
+    } else {
+#pragma unroll
+      for (int half = 0; half < (KIND == T64 ? 2 : 1); half++) {
+        const float *acc = half ? acc1 : acc0;
+        const float pw = Lpw[32 * half + r32];
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+          *reinterpret_cast<float4 *>(yt + (32 * half + r32) * YVS + 32 * wave + 8 * q + 4 * hh) =
+              make_float4(pw * acc[4 * q], pw * acc[4 * q + 1], pw * acc[4 * q + 2],
+                          pw * acc[4 * q + 3]);
+      }
+    }
+    __syncthreads();
+    const bool vec = (a.N & 3) == 0;
+    const int64_t n = (int64_t)slice * WROWS + 4 * r32;
+#pragma unroll
+    for (int u = 0; u < ROWS / 8; u++) {
+      const int m = 8 * u + 2 * wave + hh, p = Lpair[m];
+      if (p < 0 || n >= a.N) continue;
+      const float4 v = *reinterpret_cast<const float4 *>(yt + m * YVS + 4 * r32);
+      float *yp = a.y + (int64_t)p * a.N + n;
+      if (vec) {
+        *reinterpret_cast<float4 *>(yp) = v;
+      } else {
+        yp[0] = v.x;
+        if (n + 1 < a.N) yp[1] = v.y;
+        if (n + 2 < a.N) yp[2] = v.z;
+        if (n + 3 < a.N) yp[3] = v.w;
+      }
+    }
+  }
 }
 
 template <bool GATEUP, bool SYM>
@@ -611,8 +611,6 @@ __global__ __launch_bounds__(MNT) __attribute__((amdgpu_waves_per_eu(SYM ? 2 : 3
 }
 
 }  // namespace
-
-int mfma_tile_rows() { return MT; }
 
 int mfma_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint32_t *xa, const float *xd,
                 const int32_t *meta, const int32_t *perm, const int4 *tiles, float *h,

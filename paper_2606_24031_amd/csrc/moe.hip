@@ -38,7 +38,6 @@ int small_down(const uint8_t *w_d, const uint8_t *ws_d, const uint8_t *hs, const
                const int32_t *perm, const int4 *chunks, const float *topk_w,
                const float *shared_w, float *y, int64_t maxchunks, int64_t T, int64_t H,
                int64_t I, int64_t E, int64_t k, bool sym, hipStream_t s);
-int mfma_tile_rows();
 int mfma_gateup(const uint8_t *w_gu, const uint8_t *ws_gu, const uint32_t *xa, const float *xd,
                 const int32_t *meta, const int32_t *perm, const int4 *tiles, float *h,
                 uint8_t *hq, uint32_t *ha, float *hd, int64_t maxtiles, int64_t T, int64_t H,
@@ -827,13 +826,18 @@ struct GroupedWs {
   float *xd, *hd;           // ... and scales
 };
 
+// (sym: only calls of up to 1024 experts, the split route's modes.)
 template <int MODE>
 void launch_prep(unsigned nroute, unsigned nq, size_t lds, bool sym, const RouteArgs &ra,
                  const Q8Args &qa, hipStream_t s) {
-  if (sym)
-    prep_kernel<MODE, true><<<dim3(nroute + nq), dim3(ROUTE_T), lds, s>>>(ra, qa, (int)nroute);
-  else
-    prep_kernel<MODE, false><<<dim3(nroute + nq), dim3(ROUTE_T), lds, s>>>(ra, qa, (int)nroute);
+  const dim3 grid(nroute + nq);
+  if constexpr (MODE >= 2) {
+    if (sym) {
+      prep_kernel<MODE, true><<<grid, dim3(ROUTE_T), lds, s>>>(ra, qa, (int)nroute);
+      return;
+    }
+  }
+  prep_kernel<MODE, false><<<grid, dim3(ROUTE_T), lds, s>>>(ra, qa, (int)nroute);
 }
 
 // The grouped layer (T > 1): route and quantize, gate/up, down, combine.  sym:
