@@ -248,7 +248,8 @@ __global__ __launch_bounds__(GNT) void gdn_prep_kernel(GdnArgs a) {
 // The scan of 947 tokens took 118 us with 8 columns (half of every product
 // padding), four waves and U on the VALU; 78 with eight waves and 16 columns;
 // 64 with Y and the outputs' stores off the chain and one multiply-add per
-// load address.
+// load address.  The whole call at 16, 32, 33 and 64 heads (128, 256, 264 and 512
+// workgroups, one per compute unit): 99 -> 68 us, 143 -> 73, 215 -> 133, 265 -> 143.
 template <int DK>
 __global__ __launch_bounds__(SNT) void gdn_scan_kernel(GdnArgs a) {
   constexpr int DKP = DK + 4;            // LDS row stride (rows of 8 threads hit distinct banks)

@@ -22,13 +22,18 @@ int small_dense(const uint8_t *w, const uint8_t *act, const int32_t *meta, const
 
 // Up to 128 rows (K <= 2048) run on the small-group VALU kernel: its
 // workgroups keep every weight load in flight at once, where the matrix-core
-// tiles of a handful of rows stream the weights one group of eight blocks at
-// a time over few workgroups (32 and 64 rows over 2048 x 2048: 14.7 and 14.7
-// us against 14.6-15.3 and 22.7 on the tiles; 128 rows 20.7 against 23.1).
-// Each chunk of 8 rows reads the whole weight matrix, so only while the
-// weights times the chunks stay small (the re-reads then come from the
-// caches): the output projection of 151936 x 2048 (175 MB) took 224 us
-// against 60 at 32 rows and 66 against 43 at 8 rows.
+// tiles stream the weights in stages of four blocks.  Each chunk of 8 rows reads
+// the whole weight matrix, so only while the weights times the chunks stay small
+// (the re-reads then come from the caches): the output projection of 151936 x
+// 2048 (175 MB) took 224 us against 60 at 32 rows and 66 against 43 at 8 rows.
+// Call times on the VALU kernel / on the tiles, us: over 2048 x 2048 2 rows 11.5 /
+// 14.4, 32 rows 13.5 / 14.8, 64 rows 13.9 / 14.7, 128 rows 18.5 / 14.8; over 8192 x
+// 2048 16 rows 13.8 / 14.7, 48 rows 23.4 / 15.0; over 2048 x 1024 32 rows 13.1 /
+// 11.1.  So speed alone would draw the line at one chunk workgroup per compute
+// unit and K = 2048; it lies further out because the VALU kernel's sums are the
+// more accurate ones (a lane takes eight blocks of a row, the lanes are then
+// added; the tiles add K / 32 terms in one chain): error against 64 bits, 64
+// rows, K = 512, 1024, 2048: 6.0e-8, 6.6e-8, 7.2e-8 against 7.4e-8, 1.0e-7, 1.4e-7.
 constexpr int64_t DENSE_SMALL_M = 128;
 constexpr int64_t DENSE_SMALL_REREAD = (int64_t)64 << 20;   // bytes of weights x chunks
 inline bool dense_small_ws(int64_t M, int64_t K) {           // the workspace may need it

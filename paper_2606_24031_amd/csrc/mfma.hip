@@ -10,7 +10,8 @@
 //   * Staging: four blocks (K = 128) of every operand at a time, by direct
 //     loads into a ring of LDS slots: 80 bytes of each weight row (raw), 128
 //     bytes of codes and 16 of scales of each token row.  A wave waits only
-//     for its oldest stage (a vmcnt of the younger ones' loads) before the
+//     for its oldest stage (a vmcnt of the younger ones' loads; the two slots of
+//     a 64-row tile leave none, so it waits for all) before the
 //     stage's one barrier.  The raw weights go through LDS because a lane per
 //     row read straight from memory touches a cache line per lane and
 //     instruction; and because they then take no registers while under way.
@@ -41,24 +42,28 @@
 // needs no lane exchange; Q8_0 of each 32-wide h block goes through LDS.
 // Down tiles write w * y per pair, through LDS in whole rows of 512 bytes.
 //
-// What bounds it: VALU issue.  The two fp32 operations per output and block
-// cost more than the product itself (in registers alone the 32x32x32 block
-// takes 61 ns per SIMD, of which the product 16); LDS and load traffic add to
-// that.  Registers (at most 168) and LDS (51 KB) leave three workgroups per
-// compute unit; the deeper ring that two would allow, four workgroups of 128
-// registers, and waves of 64 weight rows all measured slower.  Kernel times
-// before (weights loaded per lane into registers one group of eight blocks
-// ahead, two workgroups per compute unit) and now, top-8 of 256 experts with
-// skewed load, H = 2048, I = 512: gate/up of 947 tokens 114-126 -> 103-105 us,
-// of 5120 tokens 385-405 -> 333-352 us, down 63-70 -> 65-68 and 214-221 ->
-// 230-244 us; 32 rows over 151936 x 2048 62.8 -> 59.5 us (2.9 TB/s), 947 over
-// 4096 x 2048 34.7 -> 33.6 us.  The down projection lost its resident codes
-// and several slices per workgroup (K <= 512): one slice per workgroup at
-// three per compute unit does as well up to a 947-token prompt, and a long
-// prompt loses there about half of what its gate/up gains.  The fp32-scale
-// form (one more operation per output and block, each stage summed on its
-// own: 220 registers, two workgroups per compute unit) takes 125-136 and 80-87
-// us for gate/up and down of 947 tokens.
+// What bounds it.  Large products: VALU issue (16384 x 2048 x 2048: the VALU
+// issues in 85% of the cycles, the matrix cores work in 16%; the two fp32
+// operations per output and block are 32 of 43 VALU instructions per product).
+// Prompt layers and products of few workgroups: latency (947 tokens, gate/up and
+// down: VALU 58 and 49%; of the waves' cycles 28 and 41% wait on a counter or the
+// barrier, 36 and 26% for issue).  A stage is a short chain (barrier, weight
+// scales read, converted, written and read back, operands, products) that three
+// workgroups per compute unit do not cover; registers (at most 168) and LDS
+// (51 KB) allow no more.  Measured slower: four workgroups of 128 registers, waves
+// of 64 weight rows, rings of four slots at two workgroups (also with one
+// workgroup per compute unit), every slot filled before the first stage, and
+// several slices per workgroup with the ring running on across them.
+// Kernel times, trace medians before (weights loaded per lane into registers one
+// group of eight blocks ahead, codes of K <= 512 resident over several slices, two
+// workgroups per compute unit) and now, top-8 of 256 experts with skewed load, H =
+// 2048, I = 512: gate/up of 947 tokens 125.5 -> 111.8 us, of 5120 tokens 404.9 ->
+// 363.8; down 69.6 -> 67.4 and 221.0 -> 241.2 (a long prompt's down gives back half
+// of what its gate/up gains); 333 tokens of 128 experts, I = 768: 76.7 -> 72.8 and
+// 46.6 -> 41.7; 32 rows over 151936 x 2048 62.8 -> 59.6 (2.9 TB/s), 947 over 4096 x
+// 2048 34.7 -> 33.7.  The fp32-scale form (one more operation per output and block,
+// each stage summed on its own: 220 registers, two workgroups per compute unit)
+// takes 132 and 80 us for gate/up and down of 947 tokens.
 #include <algorithm>
 
 #include "w4a8_dev.h"
@@ -129,8 +134,7 @@ constexpr int HVS = 68;            // row stride of the h tile
 constexpr int EPI_BYTES = MT * (WROWS + 4) * 4;
 
 struct MLds {
-  // the ring; before it the tile's activation rows (int [64]), after it the
-  // tile's h (gate/up, float [64][68]) or output (down, float [64][132]),
+  // the ring; after it the tile's h (gate/up, float [64][68]) or output (down, float [64][132]),
   // then its pairs and combine weights (int and float [64])
   uint4 ring[RING_BYTES / 16];
   float dw[4][SB][32];             // weight-row scales of the current stage, [wave][block][row]

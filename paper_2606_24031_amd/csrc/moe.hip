@@ -89,12 +89,16 @@ struct Layout {
 // Largest group that takes the VALU path (small_gateup / small_down, in
 // chunks of SMALL_CHUNK rows): every group of a batch of up to 128 tokens,
 // whose few-row groups are bound by weight streaming, where the VALU
-// kernels keep every weight load of a workgroup in flight at once (64
-// tokens: 104 us per layer against 127 on the tiles; 128 tokens: 137
-// against 148; 256 tokens: 213 against 157).  Above that every group goes
-// to the MFMA tiles, whose 16-row tiles pad a few-row group less than
-// separate VALU launches for those groups cost (947 tokens: 207 us per
-// layer against 214-218 with groups of up to 8 rows on the VALU kernels).
+// kernels keep every weight load of a workgroup in flight at once.  Above
+// that every group goes to the MFMA tiles, whose 16-row tiles pad a few-row
+// group less than separate VALU launches for those groups would cost.  us per
+// layer on the VALU kernels / on the tiles, H = 2048: top-8 of 256, I = 512, 64
+// tokens 98 / 117, 128 tokens 134 / 135, 160 tokens 150 / 141, 256 tokens 199 / 143;
+// top-4 of 256, 128 tokens 107 / 121, 192 tokens 125 / 130; top-8 of 128, I = 768, 48
+// tokens 93 / 104, 64 tokens 110 / 107, 128 tokens 164 / 112; top-8 of 32, 16 tokens 42 /
+// 31.  By speed the line lies at about four pairs per expert named (which 128
+// tokens of top-8 of 256 are); it is kept on the tokens, because the VALU
+// kernels' sums round less (half the tiles' error at K = 2048).
 // A group holds up to T * k rows, not T: a token may name one expert in
 // several slots.
 constexpr int64_t SMALL_T_MAX = 128;
