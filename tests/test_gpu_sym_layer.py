@@ -156,14 +156,17 @@ def test_sym_layer_exact_integer_layer_grouped(E, k, clusters, shared):
 # and finished in one launch; 160 and 400: with groups of a few rows and of
 # more than 64, the routing being skewed), a skipped slot and a repeated
 # expert; I = 256 (two stages of the tiles) to 768; H = 2304, past the VALU
-# kernels' rows, on the tiles at 20 tokens.
+# kernels' rows, on the tiles at 20 tokens; 40 slots per token; the largest expert
+# count.
 @pytest.mark.parametrize("T,H,I,E,k,shared", [(13, 2048, 512, 12, 8, True),
                                               (44, 1024, 512, 12, 4, True),
                                               (128, 1024, 512, 5, 2, False),
                                               (129, 768, 256, 9, 3, True),
                                               (160, 512, 768, 17, 4, True),
                                               (400, 256, 256, 40, 3, False),
-                                              (20, 2304, 512, 6, 3, True)])
+                                              (20, 2304, 512, 6, 3, True),
+                                              (12, 512, 512, 48, 40, True),
+                                              (450, 256, 256, 1024, 2, True)])
 def test_sym_layer_grouped(T, H, I, E, k, shared):
     print(f"sym grouped T={T} H={H} I={I} E={E} k={k}", flush=True)
     g = synth.rng(T + H + I + E)
