@@ -134,8 +134,8 @@ constexpr int HVS = 68;            // row stride of the h tile
 constexpr int EPI_BYTES = MT * (WROWS + 4) * 4;
 
 struct MLds {
-  // the ring; after it the tile's h (gate/up, float [64][68]) or output (down, float [64][132]),
-  // then its pairs and combine weights (int and float [64])
+  // the ring; after it the tile's h (gate/up, float [64][68]) or output (down,
+  // float [64][132]), then its pairs and combine weights (int and float [64])
   uint4 ring[RING_BYTES / 16];
   float dw[4][SB][32];             // weight-row scales of the current stage, [wave][block][row]
 };
